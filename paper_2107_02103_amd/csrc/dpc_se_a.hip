@@ -209,6 +209,18 @@ __device__ __forceinline__ WaveAtoms<NB> wave_atoms(const Geo& g, const int* __r
   return w;
 }
 
+// The NB consecutive atoms that all wavefronts of a workgroup share.
+template <int NB>
+__device__ __forceinline__ WaveAtoms<NB> shared_atoms(const Geo& g, int lane) {
+  WaveAtoms<NB> w;
+  const int base = (int)blockIdx.x * NB;
+#pragma unroll
+  for (int a = 0; a < NB; ++a)
+    w.idx[a] = __builtin_amdgcn_readfirstlane(base + a < g.nloc ? base + a : -1);
+  w.lanes = lane < NB && base + lane < g.nloc ? base + lane : -1;
+  return w;
+}
+
 // idx[a] for an index a in [0, NB) that is the same in every lane
 template <int NB>
 __device__ __forceinline__ int atom_of(const WaveAtoms<NB>& w, int a) {
@@ -301,6 +313,8 @@ __device__ __forceinline__ uint32_t valid_window(const Geo& g, const WaveAtoms<N
   uint32_t vm = 0;
 #pragma unroll 1
   for (int k0 = 0; k0 < 32; k0 += kGroup) {
+    // one atom: the slots of the rest of the window lie past the list
+    if (NB == 1 && wbase + kLanes * k0 >= g.nnei) break;
     int v[kGroup];
     bool in[kGroup];
 #pragma unroll
@@ -555,9 +569,9 @@ template <typename TA>
 using Pair = TA __attribute__((ext_vector_type(2)));
 
 // kOne: all atoms and neighbours have one type (one table, no blocks)
-template <typename TI, typename TA, int CPL, int NB, bool kOne>
+template <typename TI, typename TA, int CPL, int NB, bool kOne, int kSplit = 1>
 // up to 128 channels: registers capped so that 3 wavefronts fit on a SIMD
-__global__ __launch_bounds__(64 * kWaves)
+__global__ __launch_bounds__(64 * (kSplit > 1 ? kSplit : kWaves))
 __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
     const Geo g, const TI* __restrict__ coeff, const int* __restrict__ atype,
     const int* __restrict__ nlist, const TI* __restrict__ em, TA* __restrict__ T,
@@ -566,8 +580,14 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
   constexpr int kC = kLanes / NB;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const WaveAtoms<NB> wa = wave_atoms<NB, kOne>(g, atype, lane, wave);
+  constexpr bool kShared = kSplit > 1;
+  WaveAtoms<NB> wa;
+  if constexpr (kShared) wa = shared_atoms<NB>(g, lane);
+  else wa = wave_atoms<NB, kOne>(g, atype, lane, wave);
   if (wa.idx[0] < 0) return;
+  // the threads that write an atom's outputs together
+  constexpr int kOut = kShared ? 64 * kSplit : 64;
+  const int tid = kShared ? (int)threadIdx.x : lane;
   const int my_atom = lane_atom_of<NB>(wa, lane / kC);   // the atom of this lane's chunk-set slots
   const int nnei = g.nnei, m1 = g.m1, m2 = g.m2, ld = g.ld;
   const uint32_t zoff = __builtin_amdgcn_readfirstlane(wave * (uint32_t)fwd_wave_bytes<TI, TA>(m1));
@@ -585,8 +605,8 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
       const int t = __builtin_amdgcn_readfirstlane(atype[i]);
       if (t < 0 || t >= g.ntypes) {  // invalid type: the atom's outputs become NaN
         const TA nan = (TA)NAN;
-        for (int e = lane; e < m1 * 4; e += 64) T[(size_t)i * m1 * 4 + e] = nan;
-        for (int e = lane; e < m1 * m2; e += 64) D[(size_t)i * m1 * m2 + e] = nan;
+        for (int e = tid; e < m1 * 4; e += kOut) T[(size_t)i * m1 * 4 + e] = nan;
+        for (int e = tid; e < m1 * m2; e += kOut) D[(size_t)i * m1 * m2 + e] = nan;
       } else {
         ai[a] = t;
       }
@@ -610,10 +630,13 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
 
   // Chunk sets are visited cyclically from a start that differs between
   // wavefronts, so that waves sharing a SIMD are not all building (a
-  // latency-bound phase) at the same time.
+  // latency-bound phase) at the same time.  Wavefronts that share their
+  // atoms take the occupied chunk sets in turn (NB > 1), or each its share
+  // of every chunk set's runs (NB = 1).
   const int nch = (nnei + kC - 1) / kC;
-  int s0 = ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
+  int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
+  int turn = 0;
   for (int cc = 0, wbase = -1; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
     if (s0 - s0 % (kWindow / NB) != wbase) {  // window of nlist signs holding s0
       wbase = s0 - s0 % (kWindow / NB);
@@ -621,10 +644,16 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
       occ = occupied_chunks<NB>(vm);
     }
     if (!((occ >> ((s0 - wbase) / kC)) & 1)) continue;   // padding only
+    if (kShared && NB > 1 && turn++ % kSplit != wave) continue;
     const Tables tb = build_chunk_set<TI, TA, NB, false, kOne>(g, ai, my_atom, s0, wbase, vm, em, W.z, W.s, lane);
     if (tb.n == 0) continue;
-    load_coef<TI, CPL>(rs, key_offset(readlane(tb.vk, 0)), ld, voff, cfA);
-    int r = 0;
+    int r = 0, r1 = tb.nruns;
+    if constexpr (kShared && NB == 1) {
+      r = wave * tb.nruns / kSplit;
+      r1 = (wave + 1) * tb.nruns / kSplit;
+      if (r == r1) continue;
+    }
+    load_coef<TI, CPL>(rs, key_offset(readlane(tb.vk, r)), ld, voff, cfA);
     // run r with `cur` loaded; the next run's coefficients go to `nxt`
     auto run = [&](TI (&cur)[6][CPL], TI (&nxt)[6][CPL]) __attribute__((always_inline)) {
       load_coef<TI, CPL>(rs, key_offset(readlane(tb.vk, min(r + 1, kLanes - 1))), ld, voff,
@@ -667,33 +696,49 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
     };
     for (;;) {
       run(cfA, cfB);
-      if (++r == tb.nruns) break;
+      if (++r == r1) break;
       run(cfB, cfA);
-      if (++r == tb.nruns) break;
+      if (++r == r1) break;
     }
     wave_sync();
   }
 
   // T and D = T (T<)^T of each atom.  The rows go through LDS so that both
   // outputs are written in flat order, consecutive lanes to consecutive
-  // addresses; lane f of a D pass computes element f = m * m2 + n.
-  TA* sT = reinterpret_cast<TA*>(wb);
-  const int m_step = 64 / m2, n_step = 64 % m2;
+  // addresses; thread f of a D pass computes element f = m * m2 + n.
+  // Wavefronts that share their atoms add their partial rows first, in
+  // wavefront order, into the first one's LDS.
+  auto sync = [&]() __attribute__((always_inline)) {
+    if constexpr (kShared) __syncthreads();
+    else wave_sync();
+  };
+  TA* sT = reinterpret_cast<TA*>(kShared ? smem : wb);
+  const int m_step = kOut / m2, n_step = kOut % m2;
 #pragma unroll
   for (int a = 0; a < NB; ++a) {
     const int i = wa.idx[a];
     if (ai[a] < 0) continue;
-    wave_sync();
+    sync();
 #pragma unroll
     for (int h = 0; h < CPL; ++h) {
       const int m = lane * CPL + h;
       if (m < m1) {
-        Pair<TA>* d = reinterpret_cast<Pair<TA>*>(sT + m * 4);
+        Pair<TA>* d = reinterpret_cast<Pair<TA>*>(reinterpret_cast<TA*>(wb) + m * 4);
         d[0] = Pair<TA>{acc[a][h][0], acc[a][h][1]};
         d[1] = Pair<TA>{acc[a][h][2], acc[a][h][3]};
       }
     }
-    wave_sync();
+    sync();
+    if constexpr (kShared) {
+      for (int e = tid; e < m1 * 2; e += kOut) {
+        Pair<TA> v = reinterpret_cast<const Pair<TA>*>(sT)[e];
+#pragma unroll
+        for (int w = 1; w < kSplit; ++w)
+          v += reinterpret_cast<const Pair<TA>*>(smem + w * fwd_wave_bytes<TI, TA>(m1))[e];
+        reinterpret_cast<Pair<TA>*>(sT)[e] = v;
+      }
+      sync();
+    }
     TA* Ti = T + (size_t)i * m1 * 4;
     TA* Di = D + (size_t)i * m1 * m2;
     auto dot = [&](int m, int n) __attribute__((always_inline)) -> TA {
@@ -707,12 +752,12 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
     };
     if (g.pair_out) {
       // two elements per lane and store
-      for (int e = lane; e < m1 * 2; e += 64)
+      for (int e = tid; e < m1 * 2; e += kOut)
         __builtin_nontemporal_store(reinterpret_cast<const Pair<TA>*>(sT)[e],
                                     reinterpret_cast<Pair<TA>*>(Ti) + e);
-      const int ms = 128 / m2, ns = 128 % m2;
-      int m = (2 * lane) / m2, n = (2 * lane) % m2;
-      for (int f2 = lane; f2 < m1 * m2 / 2; f2 += 64) {
+      const int ms = 2 * kOut / m2, ns = 2 * kOut % m2;
+      int m = (2 * tid) / m2, n = (2 * tid) % m2;
+      for (int f2 = tid; f2 < m1 * m2 / 2; f2 += kOut) {
         int mb = m, nb = n + 1;
         if (nb == m2) {
           nb = 0;
@@ -728,9 +773,9 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
         }
       }
     } else {
-      for (int e = lane; e < m1 * 4; e += 64) __builtin_nontemporal_store(sT[e], Ti + e);
-      int m = lane / m2, n = lane % m2;
-      for (int f = lane; f < m1 * m2; f += 64) {
+      for (int e = tid; e < m1 * 4; e += kOut) __builtin_nontemporal_store(sT[e], Ti + e);
+      int m = tid / m2, n = tid % m2;
+      for (int f = tid; f < m1 * m2; f += kOut) {
         __builtin_nontemporal_store(dot(m, n), Di + f);
         m += m_step;
         n += n_step;
@@ -766,9 +811,9 @@ __host__ __device__ constexpr size_t bwd_wave_bytes() {
   return align16(sizeof(WaveLds<TI>)) + (size_t)2 * kBatch * kRedBlock;
 }
 
-template <typename TI, typename TA, int CPL, int NB, bool kOne>
+template <typename TI, typename TA, int CPL, int NB, bool kOne, int kSplit = 1>
 // up to 128 channels: registers capped so that 3 wavefronts fit on a SIMD
-__global__ __launch_bounds__(64 * kWaves)
+__global__ __launch_bounds__(64 * (kSplit > 1 ? kSplit : kWaves))
 __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
     const Geo g, const TI* __restrict__ coeff, const int* __restrict__ atype,
     const int* __restrict__ nlist, const TI* __restrict__ em, const TI* __restrict__ dT,
@@ -778,7 +823,10 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
   constexpr int PS = part_stride<TA>();
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const WaveAtoms<NB> wa = wave_atoms<NB, kOne>(g, atype, lane, wave);
+  constexpr bool kShared = kSplit > 1;
+  WaveAtoms<NB> wa;
+  if constexpr (kShared) wa = shared_atoms<NB>(g, lane);
+  else wa = wave_atoms<NB, kOne>(g, atype, lane, wave);
   if (wa.idx[0] < 0) return;
   const int my_atom = lane_atom_of<NB>(wa, lane / kC);   // the atom of this lane's chunk-set slots
   const int nnei = g.nnei, m1 = g.m1, ld = g.ld;
@@ -845,12 +893,11 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
   };
   static_assert(4 * sizeof(TA) <= sizeof(Rec<TI>), "a record slot holds one output row");
 
-  // Chunk sets are visited cyclically from a start that differs between
-  // wavefronts, so that waves sharing a SIMD are not all building (a
-  // latency-bound phase) at the same time.
+  // Chunk sets are visited as in the forward.
   const int nch = (nnei + kC - 1) / kC;
-  int s0 = ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
+  int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
+  int turn = 0;
   for (int cc = 0, wbase = -1; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
     if (s0 - s0 % (kWindow / NB) != wbase) {  // window of nlist signs holding s0
       wbase = s0 - s0 % (kWindow / NB);
@@ -858,14 +905,25 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
       occ = occupied_chunks<NB>(vm);
     }
     if (!((occ >> ((s0 - wbase) / kC)) & 1)) {   // padding only: zero rows
-      zero_rows<TA, NB>(g, ai, my_atom, s0, dR, lane);
+      if (!kShared || cc % kSplit == wave) zero_rows<TA, NB>(g, ai, my_atom, s0, dR, lane);
       continue;
     }
+    if (kShared && NB > 1 && turn++ % kSplit != wave) continue;
     const Tables tb = build_chunk_set<TI, TA, NB, true, kOne>(g, ai, my_atom, s0, wbase, vm, em, W.z, W.s, lane);
     // Each lane writes the dE/dR~ row of its own slot (zero for padding) after
     // the chunk set's runs: consecutive lanes, consecutive rows, and no store
     // ahead of the coefficient loads whose waits would then include it.
+    // Of a chunk set whose runs are shared out, a wavefront writes the records
+    // of its runs, [e_lo, e_hi) in merged order; the first one also the padding.
+    int r = 0, r1 = tb.nruns, e_lo = 0, e_hi = tb.n;
+    if constexpr (kShared && NB == 1) {
+      r = wave * tb.nruns / kSplit;
+      r1 = (wave + 1) * tb.nruns / kSplit;
+      e_lo = readlane(tb.vs, r < kLanes ? r : kLanes - 1);
+      e_hi = r1 < kLanes ? readlane(tb.vs, r1) : tb.n;
+    }
     auto write_rows = [&]() __attribute__((always_inline)) {
+      if (kShared && NB == 1 && (tb.rank < 0 ? wave > 0 : tb.rank < e_lo || tb.rank >= e_hi)) return;
       if (tb.rank >= -1) {
         TA v[4] = {(TA)0, (TA)0, (TA)0, (TA)0};
         if (tb.rank >= 0) {
@@ -876,12 +934,12 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
         store_row(dR + ((size_t)my_atom * nnei + s0 + lane % kC) * 4, v);
       }
     };
-    if (tb.n == 0) {
+    if (tb.n == 0 || (kShared && NB == 1 && r == r1)) {
+      e_hi = e_lo;            // no records: padding only
       write_rows();
       continue;
     }
-    load_coef<TI, CPL>(rs, key_offset(readlane(tb.vk, 0)), ld, voff, cfA);
-    int r = 0;
+    load_coef<TI, CPL>(rs, key_offset(readlane(tb.vk, r)), ld, voff, cfA);
     auto run = [&](TI (&cur)[6][CPL], TI (&nxt)[6][CPL]) __attribute__((always_inline)) {
       load_coef<TI, CPL>(rs, key_offset(readlane(tb.vk, min(r + 1, kLanes - 1))), ld, voff,
                          nxt);
@@ -941,12 +999,12 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
     };
     for (;;) {
       run(cfA, cfB);
-      if (++r == tb.nruns) break;
+      if (++r == r1) break;
       run(cfB, cfA);
-      if (++r == tb.nruns) break;
+      if (++r == r1) break;
     }
     if (nb > 0) {
-      reduce(tb.n - nb, nb);
+      reduce(e_hi - nb, nb);
       nb = 0;
     }
     wave_sync();
@@ -1005,15 +1063,16 @@ __host__ __device__ constexpr int mfma_slot_kib(int S, int ld, int esize = 8) {
 // share a CU (measured: 53,824 bytes leave room for two).
 constexpr int kPairDoubles = 26;   // one product in LDS: 4 rows of 6 + 2 padding
 constexpr int kMfmaWaveLds = 53312 / kWaves;
-__host__ __device__ constexpr int pair_slots(int ns) {
-  return ((kMfmaWaveLds - (int)align16(sizeof(ChunkScratch)) - 1024 * ns) /
+__host__ __device__ constexpr int pair_slots(int ns, int nb = kMfmaAtoms) {
+  // a wavefront that serves one atom holds few products at a time
+  return nb == 1 ? 8 : ((kMfmaWaveLds - (int)align16(sizeof(ChunkScratch)) - 1024 * ns) /
               (kPairDoubles * (int)sizeof(double)) / 4 * 4 > 32
               ? 32
               : (kMfmaWaveLds - (int)align16(sizeof(ChunkScratch)) - 1024 * ns) /
                     (kPairDoubles * (int)sizeof(double)) / 4 * 4);
 }
-__host__ __device__ constexpr size_t bwdm_wave_bytes(int ns) {
-  return align16(sizeof(ChunkScratch)) + (size_t)pair_slots(ns) * kPairDoubles * sizeof(double) +
+__host__ __device__ constexpr size_t bwdm_wave_bytes(int ns, int nb = kMfmaAtoms) {
+  return align16(sizeof(ChunkScratch)) + (size_t)pair_slots(ns, nb) * kPairDoubles * sizeof(double) +
          (size_t)1024 * ns;
 }
 
@@ -1154,58 +1213,105 @@ __device__ __forceinline__ void wait_copies() {
 // M1, M' are zero (loads clamped inside the atom's rows); atoms past nloc
 // get zeros.  T and dE/dD are read straight from memory (the second sum
 // re-reads dE/dD rows the first sum has just brought into the caches).
-template <int NB, int S>
-__device__ __forceinline__ void descriptor_bwd_operands(const Geo& g, const WaveAtoms<NB>& wa,
-                                                        const double* __restrict__ Tin,
-                                                        const double* __restrict__ dD, int lane,
-                                                        double (&A)[NB][S]) {
+// Part `part` of `parts` of atom i's sums: the K steps s = part (mod parts) of
+// the first sum in acc, a share of the second sum in `second`, which starts
+// from acc[0] in part 0 (so that the parts' `second` add up to A[0]).
+template <int S>
+__device__ __forceinline__ void descriptor_bwd_sums(const Geo& g, int i, const double* __restrict__ Tin,
+                                                    const double* __restrict__ dD, int lane, int part,
+                                                    int parts, double (&acc)[S], double& second) {
   typedef double D2 __attribute__((ext_vector_type(2)));
   const int m1 = g.m1, m2 = g.m2;
   const int kk = lane >> 4, b = (lane >> 2) & 3, x = lane & 3;
   const int nq = (m2 + 7) >> 3;           // 16-byte K pairs of the first sum (M' <= 16: 1 or 2)
   const int np = (m1 + 3) >> 2;           // K steps of the second sum
   const int col = 4 * x + b;              // second sum: the output channel of the lane's A row
+  const double* Ta = Tin + (size_t)i * m1 * 4;
+  const double* Da = dD + (size_t)i * m1 * m2;
+#pragma unroll
+  for (int s = 0; s < S; ++s) acc[s] = 0.0;
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    if (q >= nq) break;
+    const int n = 8 * q + 2 * kk;
+    const bool nv = n < m2;             // m2 even: n + 1 < m2 too
+    const int nc = nv ? n : 0;
+    const double b0 = nv ? Ta[nc * 4 + x] : 0.0, b1 = nv ? Ta[nc * 4 + 4 + x] : 0.0;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      if (parts > 1 && s % parts != part) continue;
+      const int m = 16 * s + 4 * x + b;
+      const bool ok = nv && m < m1;
+      const D2 v = *reinterpret_cast<const D2*>(Da + (size_t)min(m, m1 - 1) * m2 + nc);
+      acc[s] = mfma4(ok ? v.x : 0.0, b0, acc[s]);
+      acc[s] = mfma4(ok ? v.y : 0.0, b1, acc[s]);
+    }
+  }
+  second = part == 0 ? acc[0] : 0.0;
+  const bool cv = col < m2;
+  const int cc = cv ? col : 0;
+  for (int p0 = 4 * part; p0 < np; p0 += 4 * parts) {   // four K steps at a time (zeros past M1)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int mp = 4 * (p0 + u) + kk;
+      const bool ok = mp < m1;
+      const int mc = ok ? mp : 0;
+      const double bt = ok ? Ta[mc * 4 + x] : 0.0;
+      const double at = ok && cv ? __builtin_nontemporal_load(Da + (size_t)mc * m2 + cc) : 0.0;
+      second = mfma4(at, bt, second);
+    }
+  }
+}
+
+template <int NB, int S>
+__device__ __forceinline__ void descriptor_bwd_operands(const Geo& g, const WaveAtoms<NB>& wa,
+                                                        const double* __restrict__ Tin,
+                                                        const double* __restrict__ dD, int lane,
+                                                        double (&A)[NB][S]) {
 #pragma unroll
   for (int a = 0; a < NB; ++a) {
     const bool live = wa.idx[a] >= 0;
-    const int i = live ? wa.idx[a] : wa.idx[0];
-    const double* Ta = Tin + (size_t)i * m1 * 4;
-    const double* Da = dD + (size_t)i * m1 * m2;
     double acc[S];
+    descriptor_bwd_sums<S>(g, live ? wa.idx[a] : wa.idx[0], Tin, dD, lane, 0, 1, acc, A[a][0]);
 #pragma unroll
-    for (int s = 0; s < S; ++s) acc[s] = 0.0;
+    for (int s = 1; s < S; ++s) A[a][s] = acc[s];
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      if (q >= nq) break;
-      const int n = 8 * q + 2 * kk;
-      const bool nv = n < m2;             // m2 even: n + 1 < m2 too
-      const int nc = nv ? n : 0;
-      const double b0 = nv ? Ta[nc * 4 + x] : 0.0, b1 = nv ? Ta[nc * 4 + 4 + x] : 0.0;
-#pragma unroll
-      for (int s = 0; s < S; ++s) {
-        const int m = 16 * s + 4 * x + b;
-        const bool ok = nv && m < m1;
-        const D2 v = *reinterpret_cast<const D2*>(Da + (size_t)min(m, m1 - 1) * m2 + nc);
-        acc[s] = mfma4(ok ? v.x : 0.0, b0, acc[s]);
-        acc[s] = mfma4(ok ? v.y : 0.0, b1, acc[s]);
-      }
-    }
-    const bool cv = col < m2;
-    const int cc = cv ? col : 0;
-    for (int p0 = 0; p0 < np; p0 += 4) {   // four K steps at a time (zeros past M1)
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int mp = 4 * (p0 + u) + kk;
-        const bool ok = mp < m1;
-        const int mc = ok ? mp : 0;
-        const double bt = ok ? Ta[mc * 4 + x] : 0.0;
-        const double at = ok && cv ? __builtin_nontemporal_load(Da + (size_t)mc * m2 + cc) : 0.0;
-        acc[0] = mfma4(at, bt, acc[0]);
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < S; ++s) A[a][s] = live && 16 * s + (lane >> 2) < m1 ? acc[s] : 0.0;
+    for (int s = 0; s < S; ++s) A[a][s] = live && 16 * s + (lane >> 2) < g.m1 ? A[a][s] : 0.0;
   }
+}
+
+// The same for kSplit wavefronts that share their atoms: each forms one atom
+// (NB = kSplit) or its part of the one atom (NB = 1), and all read the
+// operands back from LDS (NB S + kSplit rows of 64 doubles, free until the
+// first chunk set).
+template <int NB, int S, int kSplit>
+__device__ __forceinline__ void descriptor_bwd_operands_shared(const Geo& g, const WaveAtoms<NB>& wa,
+                                                               const double* __restrict__ Tin,
+                                                               const double* __restrict__ dD, int lane,
+                                                               int wave, double* lds, double (&A)[NB][S]) {
+  static_assert(NB == 1 || NB == kSplit, "one atom, or one per wavefront");
+  const int mine = NB == 1 ? wa.idx[0] : atom_of<NB>(wa, wave);
+  double acc[S], second;
+  descriptor_bwd_sums<S>(g, mine >= 0 ? mine : wa.idx[0], Tin, dD, lane, NB == 1 ? wave : 0,
+                         NB == 1 ? kSplit : 1, acc, second);
+#pragma unroll
+  for (int s = 0; s < S; ++s)
+    if (NB > 1 || s % kSplit == wave) lds[((NB == 1 ? 0 : wave) * S + s) * kLanes + lane] = acc[s];
+  lds[(NB * S + wave) * kLanes + lane] = second;
+  __syncthreads();
+#pragma unroll
+  for (int a = 0; a < NB; ++a) {
+#pragma unroll
+    for (int s = 1; s < S; ++s) A[a][s] = lds[(a * S + s) * kLanes + lane];
+    A[a][0] = lds[(NB * S + a) * kLanes + lane];
+    if constexpr (NB == 1) {
+#pragma unroll
+      for (int w = 1; w < kSplit; ++w) A[0][0] += lds[(S + w) * kLanes + lane];
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) A[a][s] = wa.idx[a] >= 0 && 16 * s + (lane >> 2) < g.m1 ? A[a][s] : 0.0;
+  }
+  __syncthreads();
 }
 
 // TI: storage of the table, R~ and dE/dT (float64, or float32 for the
@@ -1216,8 +1322,9 @@ __device__ __forceinline__ void descriptor_bwd_operands(const Geo& g, const Wave
 //   dE/dT[m][k] = sum_{n<M'} dE/dD[m][n] T[n][k] + (m < M') sum_m' dE/dD[m'][m] T[m'][k],
 // evaluated per atom on the matrix cores straight into the A operands, so
 // dE/dT never goes to memory.
-template <typename TI, typename TO, int S, int NS, bool kOne, bool kFromD = false>
-__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(3)))
+template <typename TI, typename TO, int S, int NS, bool kOne, bool kFromD = false,
+          int NB = kMfmaAtoms, int kSplit = 1>
+__global__ __launch_bounds__(64 * (kSplit > 1 ? kSplit : kWaves)) __attribute__((amdgpu_waves_per_eu(3)))
 void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
                           const int* __restrict__ atype, const int* __restrict__ nlist,
                           const TI* __restrict__ em, const TI* __restrict__ dT,
@@ -1225,16 +1332,18 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
                           const double* __restrict__ dD = nullptr) {
   static_assert(S >= 1 && S <= 8, "K steps per channel block");
   extern __shared__ __align__(16) unsigned char smem[];
-  constexpr int NB = kMfmaAtoms;
+  constexpr bool kShared = kSplit > 1;
   constexpr int kC = kLanes / NB;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const WaveAtoms<NB> wa = wave_atoms<NB, kOne>(g, atype, lane, wave);
+  const int wave = kShared ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : (int)(threadIdx.x >> 6);
+  WaveAtoms<NB> wa;
+  if constexpr (kShared) wa = shared_atoms<NB>(g, lane);
+  else wa = wave_atoms<NB, kOne>(g, atype, lane, wave);
   if (wa.idx[0] < 0) return;
   const int my_atom = lane_atom_of<NB>(wa, lane / kC);   // the atom of this lane's chunk-set slots
   const int nnei = g.nnei, m1 = g.m1, ld = g.ld;
-  constexpr int kPairSlots = pair_slots(NS);
-  const uint32_t zoff = __builtin_amdgcn_readfirstlane(wave * (uint32_t)bwdm_wave_bytes(NS));
+  constexpr int kPairSlots = pair_slots(NS, NB);
+  const uint32_t zoff = __builtin_amdgcn_readfirstlane(wave * (uint32_t)bwdm_wave_bytes(NS, NB));
   ChunkScratch& W = *reinterpret_cast<ChunkScratch*>(smem + zoff);
   const uint32_t store = lds_addr(smem) + zoff + (uint32_t)align16(sizeof(ChunkScratch));
   unsigned char* const slot_p =
@@ -1253,7 +1362,12 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
   // A operands: dT of the wave's atoms, transposed, zero past M1
   double A[NB][S];
   int ai[NB];
-  if constexpr (kFromD) descriptor_bwd_operands<NB, S>(g, wa, Tin, dD, lane, A);
+  if constexpr (kFromD && kShared)
+    descriptor_bwd_operands_shared<NB, S, kSplit>(g, wa, Tin, dD, lane, wave, reinterpret_cast<double*>(smem), A);
+  else if constexpr (kFromD)
+    descriptor_bwd_operands<NB, S>(g, wa, Tin, dD, lane, A);
+  static_assert(!kShared || (NB * S + kSplit) * kLanes * sizeof(double) <= kSplit * bwdm_wave_bytes(NS, NB),
+                "the shared operands fit in the workgroup's LDS");
 #pragma unroll
   for (int a = 0; a < NB; ++a) {
     const int i = wa.idx[a];
@@ -1290,8 +1404,9 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
   };
 
   const int nch = (nnei + kC - 1) / kC;
-  int s0 = ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
+  int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
+  int turn = 0;
   TI pre[4];          // R~ rows of chunk set pre_s0, loaded ahead (valid slots use them)
   int pre_s0 = -1;
   for (int cc = 0, wbase = -1; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
@@ -1301,9 +1416,10 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
       occ = occupied_chunks<NB>(vm);
     }
     if (!((occ >> ((s0 - wbase) / kC)) & 1)) {   // padding only: zero rows
-      zero_rows<TO, NB>(g, ai, my_atom, s0, dR, lane);
+      if (!kShared || cc % kSplit == wave) zero_rows<TO, NB>(g, ai, my_atom, s0, dR, lane);
       continue;
     }
+    if (kShared && NB > 1 && turn++ % kSplit != wave) continue;
     int pair;
     Rec<TI> mine;
     const Tables tb = build_chunk_set<TI, double, NB, true, kOne, true>(
@@ -1311,10 +1427,13 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
     // the rows of the next chunk set are loaded during this one's last run
     const int s0n = s0 + kC < nnei ? s0 + kC : 0;
     // (not when the window already shows that set to hold padding only)
-    const bool more = cc + 1 < nch &&
+    const bool more = !(kShared && NB > 1) && cc + 1 < nch &&
                       (s0n - s0n % (kWindow / NB) != wbase || ((occ >> ((s0n - wbase) / kC)) & 1));
     double out[4] = {0.0, 0.0, 0.0, 0.0};   // this lane's dE/dR~ row
-    if (tb.n > 0) {
+    // this wavefront's runs: all, or its share (NB = 1: a run is one product)
+    const int r0 = kShared && NB == 1 ? wave * tb.nruns / kSplit : 0;
+    const int r1 = kShared && NB == 1 ? (wave + 1) * tb.nruns / kSplit : tb.nruns;
+    if (kShared ? r0 < r1 : tb.n > 0) {
       // the lanes whose records belong to pairs [base, base + np) read their products
       auto eval = [&](int base, int np) __attribute__((always_inline)) {
         if (pair >= base && pair < base + np) {
@@ -1354,8 +1473,8 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
       auto next_off = [&](int r) __attribute__((always_inline)) {
         return key_offset(readlane(tb.vk, min(r, kLanes - 1)));
       };
-      fetch(next_off(0));
-      int base = 0, np = 0;
+      fetch(next_off(r0));
+      int base = r0, np = 0;
       // run r: its coefficients are in the slot once the copy has landed;
       // after they are read, the slot takes the next run's (kLast: the
       // last run loads the next chunk set's rows instead)
@@ -1422,11 +1541,12 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
           np = 0;
         }
       };
-      for (int r = 0; r + 1 < tb.nruns; ++r) run(r, std::false_type{});
-      run(tb.nruns - 1, std::true_type{});
+      for (int r = r0; r + 1 < r1; ++r) run(r, std::false_type{});
+      run(r1 - 1, std::true_type{});
     }
     // each lane writes the dE/dR~ row of its own slot (zero for padding)
-    if (tb.rank >= -1) {
+    const bool mine_out = !(kShared && NB == 1) || (tb.rank < 0 ? wave == 0 : pair >= r0 && pair < r1);
+    if (tb.rank >= -1 && mine_out) {
       const TO o[4] = {(TO)out[0], (TO)out[1], (TO)out[2], (TO)out[3]};
       store_row(dR + ((size_t)my_atom * nnei + s0 + lane % kC) * 4, o);
     }
@@ -1493,16 +1613,34 @@ int make_geo(int nloc, int ntypes, const int* sel, int m1, int m2, const dpc_ran
   return DPC_OK;
 }
 
+// How the wavefronts of a workgroup share atoms.  Unsplit, a wavefront walks
+// the lists of its atoms alone: the least coefficient traffic per atom, but
+// one serial chain of runs, which is what a small system waits for (256 atoms
+// are 64 wavefronts on 1,024 SIMDs).  kBySet: the workgroup's wavefronts take
+// the chunk sets of a few atoms in turn.  kByRun: each takes its share of the
+// runs of one atom.  Both fetch more coefficients per atom.  `run_max` and
+// `set_max` are the atom counts up to which they win (us per call, unsplit /
+// kBySet / kByRun, M1 = 100, float64 unless noted):
+//   forward    256: 67 / 33 / 16    1,372: 70 / 38 / 37    4,000: 76 / 73 / 87    6,912: 90 / 109 / 146
+//   matrix bwd 256: 69 / 32 / 16    1,372: 72 / 39 / 35    4,000: 77 / 76 / 85    6,912: 104 / 112 / 142
+//   vector bwd (float32) 256: 48 / 25 / 16    864: 50 / 29 / 30    1,372: 51 / 33 / 34    2,048: 52 / 52 / 47
+//   forward, M1 = 200    500: 100 / 47 / 35    864: 103 / 47 / 64    2,048: 106 / 92 / 129    4,000: 117 / 177 / 250
+// (lists of 77 neighbours; with 180, kBySet wins up to about 10,000 atoms).
+enum class Split { kNone, kBySet, kByRun };
+Split split_of(int nloc, int run_max, int set_max) {
+  return nloc <= run_max ? Split::kByRun : (nloc <= set_max ? Split::kBySet : Split::kNone);
+}
+
 // Channels per lane: 1 (m1 <= 64), 2 (m1 <= 128) or 4 (m1 <= 256).
 int channels_per_lane(int m1) { return m1 <= 64 ? 1 : (m1 <= 128 ? 2 : 4); }
 
-template <typename TI, typename TA>
-int launch_fwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
-               const void* em, void* T, void* D) {
-  constexpr int NB = DPC_FWD_ATOMS_PER_WAVE;
+template <typename TI, typename TA, int NB, int kSplit>
+int launch_fwd_split(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
+                     const void* em, void* T, void* D) {
   static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "atoms per wave: 1, 2, 4 or 8");
-  const dim3 grid((g.nloc + kWaves * NB - 1) / (kWaves * NB)), block(64 * kWaves);
-  const size_t shm = kWaves * fwd_wave_bytes<TI, TA>(g.m1);
+  constexpr int waves = kSplit > 1 ? kSplit : kWaves, atoms = kSplit > 1 ? NB : kWaves * NB;
+  const dim3 grid((g.nloc + atoms - 1) / atoms), block(64 * waves);
+  const size_t shm = waves * fwd_wave_bytes<TI, TA>(g.m1);
   if (shm > kMaxLds) return DPC_ENOTSUP;
   (void)hipGetLastError();  // report only what this launch raises
   auto go = [&](auto kern) {
@@ -1510,53 +1648,98 @@ int launch_fwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
                        (const TI*)em, (TA*)T, (TA*)D);
   };
   switch (channels_per_lane(g.m1)) {
-    case 1: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 1, NB, true>) : go(se_a_fwd_kernel<TI, TA, 1, NB, false>); break;
-    case 2: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 2, NB, true>) : go(se_a_fwd_kernel<TI, TA, 2, NB, false>); break;
-    default: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 4, NB, true>) : go(se_a_fwd_kernel<TI, TA, 4, NB, false>); break;
+    case 1: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 1, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 1, NB, false, kSplit>); break;
+    case 2: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 2, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 2, NB, false, kSplit>); break;
+    default: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 4, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 4, NB, false, kSplit>); break;
   }
   return launch_status();
+}
+
+template <typename TI, typename TA>
+int launch_fwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
+               const void* em, void* T, void* D) {
+  // four channels per lane leave one wavefront per SIMD: half as many fit at once or fewer
+  switch (g.m1 <= 128 ? split_of(g.nloc, 1280, 6144) : split_of(g.nloc, 512, 2048)) {
+    case Split::kByRun: return launch_fwd_split<TI, TA, 1, 8>(s, g, coeff, atype, nlist, em, T, D);
+    case Split::kBySet: return launch_fwd_split<TI, TA, DPC_FWD_ATOMS_PER_WAVE, 4>(s, g, coeff, atype, nlist, em, T, D);
+    default: return launch_fwd_split<TI, TA, DPC_FWD_ATOMS_PER_WAVE, 1>(s, g, coeff, atype, nlist, em, T, D);
+  }
 }
 
 // M1 <= 128, float64 or mixed: the matrix-core kernel, ceil(M1 / 16) K steps
 // per channel block, an interval copied by mfma_slot_kib(S, ld, esize) loads
 // (ld lies in [16 S - 12, 16 S], so that count takes one of two values per S)
-template <typename TI, typename TO, int S, bool kFromD>
+template <typename TI, typename TO, int S, bool kFromD, int NB, int kSplit>
 void launch_mfma_s(hipStream_t s, const Geo& g, dim3 grid, dim3 block, const void* coeff,
                    const int* atype, const int* nlist, const void* em, const void* dT, void* dR,
                    const double* Tin, const double* dD) {
   constexpr int es = (int)sizeof(TI);
   const int ns = mfma_slot_kib(S, g.ld, es);
   auto go = [&](auto kern, size_t wave_bytes) {
-    hipLaunchKernelGGL(kern, grid, block, kWaves * wave_bytes, s, g, (const TI*)coeff, atype,
+    hipLaunchKernelGGL(kern, grid, block, block.x / 64 * wave_bytes, s, g, (const TI*)coeff, atype,
                        nlist, (const TI*)em, (const TI*)dT, (TO*)dR, Tin, dD);
   };
   constexpr int lo = mfma_slot_kib(S, 16 * S - 12, es);
   static_assert(mfma_slot_kib(S, 16 * S, es) <= lo + 1, "two slot sizes per S");
+  // (split workgroups always take the larger slot: latency, not LDS, limits them)
+  const bool small = kSplit == 1 && ns <= lo;
+  constexpr int hi = lo + 1, sm = kSplit == 1 ? lo : hi;
   if (g.ntypes == 1) {
-    if (ns <= lo) go(se_a_bwd_mfma_kernel<TI, TO, S, lo, true, kFromD>, bwdm_wave_bytes(lo));
-    else go(se_a_bwd_mfma_kernel<TI, TO, S, lo + 1, true, kFromD>, bwdm_wave_bytes(lo + 1));
+    if (small) go(se_a_bwd_mfma_kernel<TI, TO, S, sm, true, kFromD, NB, kSplit>, bwdm_wave_bytes(sm, NB));
+    else go(se_a_bwd_mfma_kernel<TI, TO, S, hi, true, kFromD, NB, kSplit>, bwdm_wave_bytes(hi, NB));
   } else {
-    if (ns <= lo) go(se_a_bwd_mfma_kernel<TI, TO, S, lo, false, kFromD>, bwdm_wave_bytes(lo));
-    else go(se_a_bwd_mfma_kernel<TI, TO, S, lo + 1, false, kFromD>, bwdm_wave_bytes(lo + 1));
+    if (small) go(se_a_bwd_mfma_kernel<TI, TO, S, sm, false, kFromD, NB, kSplit>, bwdm_wave_bytes(sm, NB));
+    else go(se_a_bwd_mfma_kernel<TI, TO, S, hi, false, kFromD, NB, kSplit>, bwdm_wave_bytes(hi, NB));
   }
+}
+
+template <typename TI, typename TO, bool kFromD, int NB, int kSplit>
+int launch_mfma_split(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
+                      const int* nlist, const void* em, const void* dT, void* dR,
+                      const double* Tin, const double* dD) {
+  const int S = (g.m1 + 15) / 16;
+  constexpr int waves = kSplit > 1 ? kSplit : kWaves, atoms = kSplit > 1 ? NB : kWaves * NB;
+  const dim3 grid((g.nloc + atoms - 1) / atoms), block(64 * waves);
+  (void)hipGetLastError();  // report only what this launch raises
+  switch (S) {
+#define DPC_CASE(n)                                                                                           \
+  case n:                                                                                                     \
+    launch_mfma_s<TI, TO, n, kFromD, NB, kSplit>(s, g, grid, block, coeff, atype, nlist, em, dT, dR, Tin, dD); \
+    break;
+    DPC_CASE(1) DPC_CASE(2) DPC_CASE(3) DPC_CASE(4) DPC_CASE(5) DPC_CASE(6) DPC_CASE(7) DPC_CASE(8)
+#undef DPC_CASE
+  }
+  return launch_status();
 }
 
 template <typename TI, typename TO, bool kFromD = false>
 int launch_bwd_mfma(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
                     const int* nlist, const void* em, const void* dT, void* dR,
                     const double* Tin = nullptr, const double* dD = nullptr) {
-  const int S = (g.m1 + 15) / 16;
-  constexpr int NB = kMfmaAtoms;
-  const dim3 grid((g.nloc + kWaves * NB - 1) / (kWaves * NB)), block(64 * kWaves);
+  switch (split_of(g.nloc, 1280, 6144)) {
+    case Split::kByRun: return launch_mfma_split<TI, TO, kFromD, 1, 8>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
+    case Split::kBySet: return launch_mfma_split<TI, TO, kFromD, kMfmaAtoms, 4>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
+    default: return launch_mfma_split<TI, TO, kFromD, kMfmaAtoms, 1>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
+  }
+}
+
+template <typename TI, typename TA, int NB, int kSplit>
+int launch_bwd_vec(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
+                   const void* em, const void* dT, void* dR) {
+  static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "atoms per wave: 1, 2, 4 or 8");
+  constexpr int waves = kSplit > 1 ? kSplit : kWaves, atoms = kSplit > 1 ? NB : kWaves * NB;
+  const dim3 grid((g.nloc + atoms - 1) / atoms), block(64 * waves);
+  const size_t shm = waves * bwd_wave_bytes<TI>();
+  if (shm > kMaxLds) return DPC_ENOTSUP;
   (void)hipGetLastError();  // report only what this launch raises
-  switch (S) {
-#define DPC_CASE(n)                                                                                \
-  case n:                                                                                          \
-    launch_mfma_s<TI, TO, n, kFromD>(s, g, grid, block, coeff, atype, nlist, em, dT, dR, Tin, dD); \
-    break;
-    DPC_CASE(1) DPC_CASE(2) DPC_CASE(3) DPC_CASE(4) DPC_CASE(5) DPC_CASE(6) DPC_CASE(7)
-#undef DPC_CASE
-    default: launch_mfma_s<TI, TO, 8, kFromD>(s, g, grid, block, coeff, atype, nlist, em, dT, dR, Tin, dD); break;
+  auto go = [&](auto kern) {
+    hipLaunchKernelGGL(kern, grid, block, shm, s, g, (const TI*)coeff, atype, nlist,
+                       (const TI*)em, (const TI*)dT, (TA*)dR);
+  };
+  switch (channels_per_lane(g.m1)) {
+    case 1: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 1, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 1, NB, false, kSplit>); break;
+    case 2: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 2, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 2, NB, false, kSplit>); break;
+    default: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 4, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 4, NB, false, kSplit>); break;
   }
   return launch_status();
 }
@@ -1570,22 +1753,11 @@ int launch_bwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
     if (g.m1 <= 128) return launch_bwd_mfma<TI, TA>(s, g, coeff, atype, nlist, em, dT, dR);
   }
   constexpr int NB = DPC_BWD_ATOMS_PER_WAVE;
-  static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "atoms per wave: 1, 2, 4 or 8");
-  const dim3 grid((g.nloc + kWaves * NB - 1) / (kWaves * NB)), block(64 * kWaves);
-  const int cpl = channels_per_lane(g.m1);
-  const size_t shm = kWaves * bwd_wave_bytes<TI>();
-  if (shm > kMaxLds) return DPC_ENOTSUP;
-  (void)hipGetLastError();  // report only what this launch raises
-  auto go = [&](auto kern) {
-    hipLaunchKernelGGL(kern, grid, block, shm, s, g, (const TI*)coeff, atype, nlist,
-                       (const TI*)em, (const TI*)dT, (TA*)dR);
-  };
-  switch (cpl) {
-    case 1: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 1, NB, true>) : go(se_a_bwd_kernel<TI, TA, 1, NB, false>); break;
-    case 2: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 2, NB, true>) : go(se_a_bwd_kernel<TI, TA, 2, NB, false>); break;
-    default: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 4, NB, true>) : go(se_a_bwd_kernel<TI, TA, 4, NB, false>); break;
+  switch (split_of(g.nloc, 640, 1536)) {
+    case Split::kByRun: return launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR);
+    case Split::kBySet: return launch_bwd_vec<TI, TA, NB, 4>(s, g, coeff, atype, nlist, em, dT, dR);
+    default: return launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
   }
-  return launch_status();
 }
 
 }  // namespace
