@@ -128,91 +128,160 @@ __global__ __launch_bounds__(256) void env_mat_kernel(const EnvGeo g, int chunks
 }
 
 // rev[i][s] = slot of i in the list of j = nlist[i][s], in the sel block of
-// i's type, or -1.  rev starts as -1 everywhere (fill_kernel).  A pair found
-// in both lists gives both entries, rev[i][s] = k and rev[j][k] = s, so each
-// pair is searched once, by the wavefront of its smaller atom i < j (the
-// other one skips it; a pair that only one list holds is searched by that
-// list's atom when it is the smaller one, and else stays -1, which is then
-// right).  The wavefront takes its pairs eight at a time, and for each the
-// whole wavefront reads the two 128-byte lines of j's block around where i
-// is expected (i's rank in j's list is close to j's rank in i's list: the
-// same distance orders both) and looks for i with one ballot; the eight
-// window reads are issued together.  A miss (lists in another order, ranks
-// further apart) scans j's whole block.
-constexpr int kRevGroup = 8;
-__global__ void fill_kernel(int64_t n, int v, int* __restrict__ p) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < n) p[e] = v;
+// i's type, or -1 (also for padding, j out of range and j = i).
+//
+// One wavefront per atom i.  Its slots are read a window of 512 at a time;
+// the neighbours are packed densely into LDS, and each lane then looks for i
+// in the list of a neighbour of its own: 16 entries (four 16-byte loads)
+// around the place where i is expected, j's rank in its block of i's list
+// scaled by the counts of the two blocks in i's list (the same distance
+// orders both lists).  98% of the pairs of the Cu and water systems are
+// there, 90% of the alloy's, the rest mostly in the 16 entries on either side,
+// which the lanes that missed read next.  What is still missing (lists in
+// another order) is looked for by the whole wavefront in all of the block.
+// Each lane reads a line of its own, about 34 GB of lines on 1,048,576 atoms
+// with 180 neighbours (512 slots): the kernel is bound by that traffic
+// (address unit 87% busy; 8 or 12 entries first and the misses packed again
+// gave 3.4 and 3.7 ms).  Both directions of a pair are searched, because a
+// coalesced row of results is cheaper than writing the partner's entry.
+// 13.6 ms with a search of one pair at a time by the whole wavefront, now 3.3.
+constexpr int kRevWindow = 512;
+constexpr int kRevLoads = 4;                 // 16-byte loads of one look
+constexpr int kRevLook = 4 * kRevLoads;
+constexpr int kXcds = 8;                     // workgroups go to the XCDs in turn
+
+__device__ __forceinline__ int rev_lanes_below(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
-__global__ __launch_bounds__(256) void reverse_kernel(const EnvGeo g, const int* __restrict__ atype,
+// slot in [w, w + 16) and in [b0, b1) of `row` that holds i, else -1; all 16
+// entries lie inside the row
+__device__ __forceinline__ int rev_look(const int* __restrict__ row, int w, int b0, int b1, int i) {
+  typedef int V4 __attribute__((ext_vector_type(4), aligned(4)));
+  V4 v[kRevLoads];
+#pragma unroll
+  for (int q = 0; q < kRevLoads; ++q) v[q] = *reinterpret_cast<const V4*>(row + w + 4 * q);
+  int at = -1;
+#pragma unroll
+  for (int q = kRevLook - 1; q >= 0; --q) at = v[q >> 2][q & 3] == i ? q : at;
+  at += at >= 0 ? w : 0;
+  return at >= b0 && at < b1 ? at : -1;
+}
+
+__global__ __launch_bounds__(256) void reverse_kernel(const EnvGeo g, int per_xcd,
+                                                      const int* __restrict__ atype,
                                                       const int* __restrict__ nlist,
                                                       int* __restrict__ rev) {
-  const int lane = threadIdx.x & 63;
-  const int i = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
+  __shared__ int sh_j[4][kRevWindow], sh_s[4][kRevWindow];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // each XCD takes a contiguous range of atoms: neighbours' rows stay in its L2
+  const int blk = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+  const int i = __builtin_amdgcn_readfirstlane(blk * 4 + wave);
   if (i >= g.nloc) return;
+  const int nnei = g.nnei;
+  const int* li = nlist + (size_t)i * nnei;
+  int* ri = rev + (size_t)i * nnei;
   const int t = __builtin_amdgcn_readfirstlane(atype[i]);
-  if (t < 0 || t >= g.ntypes) return;       // its slots stay -1
+  if (t < 0 || t >= g.ntypes) {
+    for (int s = lane; s < nnei; s += 64) ri[s] = -1;
+    return;
+  }
   const int b0 = g.blk[t], b1 = g.blk[t + 1];
-  const int wlo = b0, whi = b1 - 32 > b0 ? b1 - 32 : b0;     // window centres start here
-  const int* li = nlist + (size_t)i * g.nnei;
-  int* ri = rev + (size_t)i * g.nnei;
-  int jn = lane < g.nnei ? li[lane] : -1;      // the next batch's slots, loaded ahead
-  for (int s0 = 0; s0 < g.nnei; s0 += 64) {
-    const int s = s0 + lane;
-    const int j = jn;
-    jn = s + 64 < g.nnei ? li[s + 64] : -1;
-    const bool mine = j > i && j < g.nloc;
-    int found = -1, tmine = -1;       // this lane's pair: slot of i in j's list, j's type
-    uint64_t todo = __ballot(mine);
-    while (todo) {
-      int src[kRevGroup], jj[kRevGroup], tj[kRevGroup], w0[kRevGroup], v[kRevGroup];
+  int* my_j = sh_j[wave];
+  int* my_s = sh_s[wave];
+  for (int w0 = 0; w0 < nnei; w0 += kRevWindow) {
+    int v[kRevWindow / 64];
 #pragma unroll
-      for (int q = 0; q < kRevGroup; ++q) {
-        src[q] = todo ? (int)__builtin_ctzll(todo) : -1;
-        todo &= todo ? todo - 1 : 0;
-        jj[q] = src[q] >= 0 ? __builtin_amdgcn_readlane(j, src[q]) : 0;
-        tj[q] = atype[jj[q]];          // uniform: a scalar load beside the window's
-        // j's place in i's list, relative to the start of its block there
-        const int sj = s0 + (src[q] >= 0 ? src[q] : 0);
+    for (int q = 0; q < kRevWindow / 64; ++q) {
+      const int s = w0 + 64 * q + lane;
+      v[q] = s < nnei ? li[s] : -1;
+    }
+    int np = 0;
+    float cnt[DPC_MAX_TYPES];
+#pragma unroll
+    for (int u = 0; u < DPC_MAX_TYPES; ++u) cnt[u] = 0.0f;
+#pragma unroll
+    for (int q = 0; q < kRevWindow / 64; ++q) {
+      const int s = w0 + 64 * q + lane;
+      const bool ok = v[q] >= 0 && v[q] < g.nloc && v[q] != i;
+      const uint64_t m = __ballot(ok);
+      if (ok) {
+        const int p = np + rev_lanes_below(m);
+        my_j[p] = v[q];
+        my_s[p] = s;
+      } else if (s < nnei) {
+        ri[s] = -1;
+      }
+      np += __popcll(m);
+      if (g.ntypes > 1 && m) {
+#pragma unroll
+        for (int u = 0; u < DPC_MAX_TYPES; ++u)
+          if (u < g.ntypes) cnt[u] += (float)__popcll(__ballot(ok && s >= g.blk[u] && s < g.blk[u + 1]));
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    float own = 0.0f;
+#pragma unroll
+    for (int u = 0; u < DPC_MAX_TYPES; ++u) own = u == t ? cnt[u] : own;
+    for (int p0 = 0; p0 < np; p0 += 64) {
+      const bool live = p0 + lane < np;
+      const int p = live ? p0 + lane : 0;
+      const int j = my_j[p], s = my_s[p];
+      int rank = s;                    // of j in its block, scaled to i's block in j's list
+      if (g.ntypes > 1) {
         int bs = 0;
+        float c = cnt[0];
 #pragma unroll
-        for (int u = 1; u < DPC_MAX_TYPES; ++u) bs = (u < g.ntypes && sj >= g.blk[u]) ? g.blk[u] : bs;
-        // 32 slots centred where i is expected, clamped into the block, read
-        // as the two 32-entry groups of the row that hold them
-        const int c = b0 + (sj - bs) - 16;
-        const int ca = c < wlo ? wlo : (c > whi ? whi : c);
-        w0[q] = ca & ~31;
-        // every lane reads an entry inside j's row; those outside the block are masked
-        const int k = w0[q] + lane;
-        v[q] = nlist[(size_t)jj[q] * g.nnei + (k < g.nnei ? k : g.nnei - 1)];
-        v[q] = k >= b0 && k < b1 ? v[q] : -1;
-      }
-#pragma unroll
-      for (int q = 0; q < kRevGroup; ++q) {
-        if (src[q] < 0) break;
-        const uint64_t hit = __ballot(v[q] == i);
-        int kk = hit ? w0[q] + (int)__builtin_ctzll(hit) : -1;
-        for (int c0 = b0; kk < 0 && c0 < b1; c0 += 64) {   // not in the window: the whole block
-          const int k = c0 + lane;
-          const int e = k < b1 ? nlist[(size_t)jj[q] * g.nnei + k] : -1;
-          const uint64_t h = __ballot(e == i);
-          kk = h ? c0 + (int)__builtin_ctzll(h) : -1;
+        for (int u = 1; u < DPC_MAX_TYPES; ++u) {
+          const bool in = u < g.ntypes && s >= g.blk[u];
+          bs = in ? g.blk[u] : bs;
+          c = in ? cnt[u] : c;
         }
-        if (lane == src[q]) {
-          found = kk;
-          tmine = tj[q];
+        rank = (int)(((float)(s - bs) + 0.5f) * own * __builtin_amdgcn_rcpf(fmaxf(c, 1.0f)));
+      }
+      const int* row = nlist + (size_t)j * nnei;
+      int found = -1;
+      if (nnei >= kRevLook) {
+        // the look's first entry: inside the block where that holds 16, and inside the row
+        const int lo = min(b0, nnei - kRevLook), hi = max(lo, b1 - kRevLook);
+        const int w = min(max(b0 + rank - kRevLook / 2, lo), hi);
+        found = rev_look(row, w, b0, b1, i);
+        if (__ballot(live && found < 0)) {
+          if (live && found < 0) {
+            const int wl = max(w - kRevLook, lo), wh = min(w + kRevLook, hi);
+            const int f0 = rev_look(row, wl, b0, b1, i), f1 = rev_look(row, wh, b0, b1, i);
+            found = f0 >= 0 ? f0 : f1;
+          }
         }
       }
+      uint64_t todo = __ballot(live && found < 0);
+      while (todo) {                   // the whole block, 512 entries per round trip
+        const int src = (int)__builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int* r = nlist + (size_t)__builtin_amdgcn_readlane(j, src) * nnei;
+        int kk = -1;
+        for (int c0 = b0; kk < 0 && c0 < b1; c0 += kRevWindow) {
+          int e[kRevWindow / 64];
+#pragma unroll
+          for (int q = 0; q < kRevWindow / 64; ++q) {
+            const int k = c0 + 64 * q + lane;
+            e[q] = k < b1 ? r[k] : -1;
+          }
+#pragma unroll
+          for (int q = kRevWindow / 64 - 1; q >= 0; --q) {
+            const uint64_t h = __ballot(e[q] == i);
+            kk = h ? c0 + 64 * q + (int)__builtin_ctzll(h) : kk;
+          }
+        }
+        if (lane == src) found = kk;
+      }
+      if (live) ri[s] = found;
     }
-    // one store instruction each per batch: the found slots, and their
-    // reverses, j's slot in i's list, where it lies in the block of j's
-    // type (where that search would look)
-    if (found >= 0) {
-      ri[s] = found;
-      if (tmine >= 0 && tmine < g.ntypes && s >= g.blk[tmine] && s < g.blk[tmine + 1])
-        rev[(size_t)j * g.nnei + found] = s;
-    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 }
 
@@ -400,8 +469,8 @@ extern "C" int dpc_nlist_reverse(void* stream, int nloc, int ntypes, const int* 
   if ((nslot + 255) / 256 >= (int64_t(1) << 31)) return DPC_ENOTSUP;
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();
-  hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((nslot + 255) / 256)), dim3(256), 0, s, nslot, -1, rev);
-  hipLaunchKernelGGL(reverse_kernel, dim3((nloc + 3) / 4), dim3(256), 0, s, g, atype, nlist, rev);
+  const int blocks = (nloc + 3) / 4, per_xcd = (blocks + kXcds - 1) / kXcds;
+  hipLaunchKernelGGL(reverse_kernel, dim3(per_xcd * kXcds), dim3(256), 0, s, g, per_xcd, atype, nlist, rev);
   return dpc_internal_launch_status();
 }
 
