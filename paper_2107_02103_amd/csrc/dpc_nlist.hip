@@ -32,13 +32,16 @@
 namespace {
 
 constexpr int kNlWaves = 4;      // wavefronts (atoms) per workgroup of the list kernel
-constexpr int kNlCap = 1024;     // neighbours within rc one wavefront keeps (12 KB of LDS)
+constexpr int kNlCap = 1024;     // neighbours within rc an atom may have
+constexpr int kNlKeep = 512;     // of these, what one wavefront's own LDS holds
 constexpr int kScanThreads = 1024;
 
 struct alignas(16) NlAtom {      // an atom in cell order
-  double x, y, z;
-  int j, type;
+  double x, y, z;                // x is NaN for an atom of an invalid type: never a neighbour
+  int j;                         // index | kOutside when the position is outside [0, box)
+  int type;
 };
+constexpr int kOutside = 1 << 30;
 
 // A neighbour within r_c as kept in LDS: the bits of r2 (>= 0: ordered like
 // the value) in one array, type and index packed as type << 28 | j in another
@@ -49,7 +52,9 @@ constexpr uint32_t kJMask = (1u << kJBits) - 1;
 struct NlGeo {
   int nloc, ntypes, nnei, nc, ncell;
   int lo_off, n_off;             // stencil offsets per axis: lo_off .. lo_off + n_off - 1
+  int type_buckets;              // r2 buckets per type in the ranking
   double box, rc2, inv_cs, inv_box;
+  double bucket_scale;           // buckets per unit of r2
   int sel[DPC_MAX_TYPES];
   int blk[DPC_MAX_TYPES + 1];    // first slot of each type block
 };
@@ -66,6 +71,13 @@ __device__ __forceinline__ double min_image(double d, const NlGeo& g) {
   double n = rint(q);
   if (!(fabs(q - n) < 0.499999 && fabs(q) < 1048576.0)) n = rint(d / g.box);
   return d - g.box * n;
+}
+
+// all three coordinates in [0, box): cell_axis wraps nothing
+__device__ __forceinline__ bool in_box(const double* p, const NlGeo& g) {
+#pragma clang fp contract(off)
+  return p[0] >= 0.0 && p[0] < g.box && p[1] >= 0.0 && p[1] < g.box && p[2] >= 0.0 && p[2] < g.box &&
+         p[0] / g.box < 1.0 && p[1] / g.box < 1.0 && p[2] / g.box < 1.0;
 }
 
 __device__ __forceinline__ int cell_axis(double x, const NlGeo& g) {
@@ -130,8 +142,9 @@ __global__ void nl_scatter_kernel(const NlGeo g, const double* __restrict__ coor
   a.x = c[0];
   a.y = c[1];
   a.z = c[2];
-  a.j = i;
+  a.j = i | (in_box(c, g) ? 0 : kOutside);
   a.type = atype[i];
+  if (a.type < 0 || a.type >= g.ntypes) a.x = (double)NAN;
   sorted[p] = a;
 }
 
@@ -161,172 +174,310 @@ __device__ __forceinline__ int lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
 }
 
-// one wavefront per atom
-__global__ __launch_bounds__(64 * kNlWaves) void nl_list_kernel(
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
+}
+
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+constexpr int kNlPer = kNlKeep / 64, kNlBuckets = 256;
+
+// One wavefront per atom.  Both halves are bound by vector issue.
+//   Candidates: the atoms of the 27 cells, 64 at a time.  Their periodic
+// image follows from the cells (no rounding of d / box per component), and
+// most batches need none.  1,048,576 atoms, 1,160 candidates and 180
+// neighbours each: 27 batches of one column's atoms with a rounded quotient
+// each, and every neighbour compared with every other for its rank, took
+// 10.8 ms; 19 full batches and the buckets take 3.7 ms (VALU 80% busy).
+//   Ranks: neighbours are counted into buckets of equal width in r2 (per
+// type), the buckets' starts are summed over the lanes, each neighbour moves
+// to its bucket, and its rank inside the bucket (one or two neighbours; a
+// whole shell in a perfect crystal) comes from comparing with the bucket only.
+//   An atom with more neighbours than a wavefront's own LDS holds is done
+// after the others of its workgroup, with all of the workgroup's LDS: so 20
+// wavefronts share a CU and not 12.
+template <bool kOne>
+__global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(5))) void nl_list_kernel(
     const NlGeo g, const double* __restrict__ coord, const int* __restrict__ cell_of,
     const int* __restrict__ start, const NlAtom* __restrict__ sorted, int* __restrict__ nlist,
     int* __restrict__ status) {
 #pragma clang fp contract(off)
-  __shared__ uint64_t cand_r2[kNlWaves][kNlCap + 4];
-  __shared__ uint32_t cand_jt[kNlWaves][kNlCap + 4];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * kNlWaves + wave));
-  if (i >= g.nloc) return;
-  uint64_t* my_r2 = cand_r2[wave];
-  uint32_t* my_jt = cand_jt[wave];
+  static_assert(kNlWaves * kNlKeep >= kNlCap + 4, "the workgroup's LDS holds one long list");
+  __shared__ uint64_t cand_r2[kNlWaves * kNlKeep];
+  __shared__ uint32_t cand_jt[kNlWaves * kNlKeep];
+  __shared__ uint32_t buckets[kNlWaves][kNlBuckets];
+  __shared__ int longer[kNlWaves];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ntypes = kOne ? 1 : g.ntypes;
+  const bool active = (int)(blockIdx.x * kNlWaves) + wave < g.nloc;
+  // past the last atom: the last one again, for the barriers' sake; nothing is written
+  const int i = active ? (int)(blockIdx.x * kNlWaves) + wave : g.nloc - 1;
+  uint64_t* my_r2 = cand_r2 + wave * kNlKeep;
+  uint32_t* my_jt = cand_jt + wave * kNlKeep;
   const double xi = coord[3 * (size_t)i], yi = coord[3 * (size_t)i + 1], zi = coord[3 * (size_t)i + 2];
   const int ci = __builtin_amdgcn_readfirstlane(cell_of[i]);
   const int cx = ci / (g.nc * g.nc), cy = (ci / g.nc) % g.nc, cz = ci % g.nc;
+  // the periodic images follow from the cells only with three or more cells
+  // per axis and positions inside the box
+  const double pi[3] = {xi, yi, zi};
+  const bool by_cell = g.nc >= 3 && in_box(pi, g);
 
   // candidates within rc, in the order they are met (n may pass kNlCap:
   // the extra ones are counted, not kept).  The stencil's cells are read as
   // spans of `sorted`: the cells of one (x, y) column that are consecutive
   // in z are consecutive there too, so a column is one span, or two where
   // it wraps around the box.  Lane k < 2 n_off^2 holds span k (column k / 2,
-  // part k % 2, possibly empty); the loop walks the spans 64 atoms at a time
-  // and loads the next batch before it works on the current one.
+  // part k % 2, possibly empty) with its periodic image: two bits per axis,
+  // n + 1 with d = x_j - x_i - n box.  An atom within rc of i in the image n
+  // lies in the cell that is met with that n: i is then within rc of the same
+  // face, so in the cell beside it.
   const int nsp = 2 * g.n_off * g.n_off;
-  int sp0 = 0, sp1 = 0;
+  int sp0 = 0, sp1 = 0, img = 1 | 1 << 2 | 1 << 4;
   if (lane < nsp) {
     const int col = lane >> 1, part = lane & 1;
-    const int ax = (cx + g.lo_off + col / g.n_off + g.nc) % g.nc;
-    const int ay = (cy + g.lo_off + col % g.n_off + g.nc) % g.nc;
+    const int rx = cx + g.lo_off + col / g.n_off, ry = cy + g.lo_off + col % g.n_off;
+    const int ax = (rx + g.nc) % g.nc, ay = (ry + g.nc) % g.nc;
     const int base = (ax * g.nc + ay) * g.nc;
-    int c0 = 0, c1 = 0;                 // cells [c0, c1) of this column
+    int c0 = 0, c1 = 0, nz = 0;         // cells [c0, c1) of this column
     if (g.nc < 3) {
       if (part == 0) c1 = g.nc;
     } else if (cz > 0 && cz < g.nc - 1) {
       if (part == 0) { c0 = cz - 1; c1 = cz + 2; }
     } else if (cz == 0) {
-      if (part == 0) { c0 = g.nc - 1; c1 = g.nc; } else { c0 = 0; c1 = 2; }
+      if (part == 0) { c0 = g.nc - 1; c1 = g.nc; nz = 1; } else { c0 = 0; c1 = 2; }
     } else {
-      if (part == 0) { c0 = g.nc - 2; c1 = g.nc; } else { c0 = 0; c1 = 1; }
+      if (part == 0) { c0 = g.nc - 2; c1 = g.nc; } else { c0 = 0; c1 = 1; nz = -1; }
     }
     sp0 = start[base + c0];
     sp1 = start[base + c1];
+    const int nx = rx < 0 ? 1 : (rx >= g.nc ? -1 : 0), ny = ry < 0 ? 1 : (ry >= g.nc ? -1 : 0);
+    img = (nx + 1) | (ny + 1) << 2 | (nz + 1) << 4;
   }
-  // the first batch at or after (span s, atom b) that holds atoms
-  auto advance = [&](int& s, int& b, int& e) __attribute__((always_inline)) {
-    while (b >= e && ++s < nsp) {
-      b = __builtin_amdgcn_readlane(sp0, s);
-      e = __builtin_amdgcn_readlane(sp1, s);
+  // candidate c of the spans' concatenation is atom c - before + sp0 of the
+  // span that holds it; lane k: first candidate after span k, and sp0 - before
+  const int upto = wave_scan(sp1 - sp0), shift = sp1 - upto;
+  const int total = __builtin_amdgcn_readlane(upto, 63);
+  int sp = 0;                              // span that holds the batch's first candidate
+  // this lane's atom of the batch from candidate c0 on, and its image
+  auto locate = [&](int c0, int& at, int& im) __attribute__((always_inline)) {
+    const int c = c0 + lane;
+    while (__builtin_amdgcn_readlane(upto, sp) <= c0) ++sp;    // c0 < total
+    at = c + __builtin_amdgcn_readlane(shift, sp);
+    im = __builtin_amdgcn_readlane(img, sp);
+    int end = __builtin_amdgcn_readlane(upto, sp);
+    for (int k = sp + 1; end <= c0 + 63 && k < nsp; ++k) {
+      const int sh = __builtin_amdgcn_readlane(shift, k), m = __builtin_amdgcn_readlane(img, k);
+      at = c >= end ? c + sh : at;
+      im = c >= end ? m : im;
+      end = __builtin_amdgcn_readlane(upto, k);
     }
+    at = c < total ? at : 0;               // every lane loads an atom of the array
   };
-  int n = 0;
-  int s = 0, b = __builtin_amdgcn_readlane(sp0, 0), e = __builtin_amdgcn_readlane(sp1, 0);
-  advance(s, b, e);
-  NlAtom cur = sorted[s < nsp ? min(b + lane, g.nloc - 1) : 0];
-  while (s < nsp) {
-    int s2 = s, b2 = b + 64, e2 = e;
-    advance(s2, b2, e2);
-    // every lane loads (an index inside the array), so that no load is conditional
-    const NlAtom nxt = sorted[s2 < nsp ? min(b2 + lane, g.nloc - 1) : 0];
-    bool ok = false;
-    uint64_t kr2 = 0;
-    uint32_t kjt = 0;
-    if (b + lane < e) {
-      const double dx = min_image(cur.x - xi, g);
-      const double dy = min_image(cur.y - yi, g);
-      const double dz = min_image(cur.z - zi, g);
+  // the first `cap` neighbours go to my_r2, my_jt; all are counted
+  auto collect = [&](int cap) __attribute__((always_inline)) {
+    int n = 0, im = 0, at = 0;
+    sp = 0;
+    if (total > 0) locate(0, at, im);
+    NlAtom cur = sorted[at];
+    for (int c0 = 0; c0 < total; c0 += 64) {
+      const int im0 = im;
+      if (c0 + 64 < total) locate(c0 + 64, at, im);
+      const NlAtom nxt = sorted[at];
+      const bool in = c0 + lane < total;
+      double dx = cur.x - xi, dy = cur.y - yi, dz = cur.z - zi;
+      if (!by_cell || __ballot(in && (cur.j & kOutside))) {
+        dx = min_image(dx, g);
+        dy = min_image(dy, g);
+        dz = min_image(dz, g);
+      } else if (__ballot(in && im0 != (1 | 1 << 2 | 1 << 4))) {
+        dx -= g.box * (double)((im0 & 3) - 1);
+        dy -= g.box * (double)(((im0 >> 2) & 3) - 1);
+        dz -= g.box * (double)((im0 >> 4) - 1);
+      }
       const double r2 = dx * dx + dy * dy + dz * dz;
-      ok = r2 < g.rc2 && cur.j != i && cur.type >= 0 && cur.type < g.ntypes;
-      kr2 = __builtin_bit_cast(uint64_t, r2);
-      kjt = (uint32_t)cur.type << kJBits | (uint32_t)cur.j;
+      const int j = cur.j & ~kOutside;
+      const bool ok = in && r2 < g.rc2 && j != i;
+      const uint64_t msk = ballot(ok);
+      const int pos = n + lanes_below(msk);
+      if (ok && pos < cap) {
+        my_r2[pos] = __builtin_bit_cast(uint64_t, r2);
+        my_jt[pos] = (uint32_t)cur.type << kJBits | (uint32_t)j;
+      }
+      n += __popcll(msk);
+      cur = nxt;
     }
-    const uint64_t msk = ballot(ok);
-    const int pos = n + lanes_below(msk);
-    if (ok && pos < kNlCap) {
-      my_r2[pos] = kr2;
-      my_jt[pos] = kjt;
-    }
-    n += __popcll(msk);
-    cur = nxt;
-    s = s2;
-    b = b2;
-    e = e2;
-  }
+    return n;
+  };
+  const int n = active ? collect(kNlKeep) : 0;
   const int m = n < kNlCap ? n : kNlCap;
-  // four entries that rank after every neighbour (type field 15) after the
-  // kept ones, so that the ranking below reads the list four at a time
-  if (lane < 4) {
-    my_r2[m + lane] = ~0ull;
-    my_jt[m + lane] = ~0u;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
-  // neighbours of each type (all of them, before truncation)
-  int cnt[DPC_MAX_TYPES];
-#pragma unroll
-  for (int t = 0; t < DPC_MAX_TYPES; ++t) cnt[t] = 0;
-  for (int b = 0; b < m; b += 64) {
-    const int q = b + lane;
-    const int ty = q < m ? (int)(my_jt[q] >> kJBits) : -1;
-#pragma unroll
-    for (int t = 0; t < DPC_MAX_TYPES; ++t) cnt[t] += __popcll(ballot(ty == t));
-  }
-
-  // slot of each kept neighbour: its rank among the neighbours of its type
-  // by (r2, j), i.e. its rank among all of them by (type, r2, j) less the
-  // number of neighbours of smaller types; up to four candidates per lane
-  // per pass over all m, four list entries per step
   int* row = nlist + (size_t)i * g.nnei;
-  for (int b = 0; b < m; b += 256) {
-    uint64_t own_r2[4];
-    uint32_t own_jt[4];
-    unsigned rank[4];
-    const int nu = min(4, (m - b + 63) / 64);   // candidate sets of this pass
+
+  int cntv = 0;                   // lane t: neighbours of type t (all of them, before truncation)
+  if (m <= kNlKeep) {
+    uint32_t* hist = buckets[wave];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = b + 64 * u + lane;
-      own_r2[u] = q < m ? my_r2[q] : ~0ull;
-      own_jt[u] = q < m ? my_jt[q] : ~0u;
-      rank[u] = 0;
+    for (int q = 0; q < kNlBuckets / 64; ++q) hist[64 * q + lane] = 0;
+    uint64_t r2[kNlPer];
+    uint32_t jt[kNlPer];
+    int bk[kNlPer], ar[kNlPer];   // bucket, and order of arrival in it
+    wave_sync();
+    const int nu = (m + 63) >> 6;
 #pragma unroll
-      for (int t = 0; t < DPC_MAX_TYPES; ++t)
-        rank[u] -= (uint32_t)t < (own_jt[u] >> kJBits) ? (unsigned)cnt[t] : 0u;
+    for (int u = 0; u < kNlPer; ++u) {
+      if (u >= nu) break;
+      const int q = 64 * u + lane;
+      r2[u] = my_r2[q];
+      jt[u] = my_jt[q];
+      bk[u] = ar[u] = 0;
+      if (q < m) {
+        // equal r2 share a bucket, larger r2 never come in an earlier one
+        bk[u] = min((int)(__builtin_bit_cast(double, r2[u]) * g.bucket_scale), g.type_buckets - 1);
+        if (!kOne) bk[u] += (int)(jt[u] >> kJBits) * g.type_buckets;
+        ar[u] = (int)atomicAdd(&hist[bk[u]], 1u);
+      }
     }
-    for (int e = 0; e < m; e += 4) {
-      uint64_t o_r2[4];
-      uint32_t o_jt[4];
+    wave_sync();
+    {
+      uint4 h = *reinterpret_cast<const uint4*>(hist + 4 * lane);
+      const int sum = (int)(h.x + h.y + h.z + h.w);
+      const uint32_t before = (uint32_t)(wave_scan(sum) - sum);
+      wave_sync();
+      *reinterpret_cast<uint4*>(hist + 4 * lane) =
+          make_uint4(before, before + h.x, before + h.x + h.y, before + h.x + h.y + h.z);
+    }
+    wave_sync();
+    // lane t: first rank of type t among all neighbours (m past the last type)
+    const int firstv = lane < ntypes ? (int)hist[lane * g.type_buckets] : m;
+    cntv = __builtin_amdgcn_ds_bpermute((lane + 1) << 2, firstv) - firstv;
+    int lo[kNlPer], hi[kNlPer];
 #pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        o_r2[v] = my_r2[e + v];
-        o_jt[v] = my_jt[e + v];
+    for (int u = 0; u < kNlPer; ++u) {
+      if (u >= nu) break;
+      lo[u] = hi[u] = 0;
+      if (64 * u + lane < m) {
+        lo[u] = (int)hist[bk[u]];
+        hi[u] = bk[u] + 1 < kNlBuckets ? (int)hist[bk[u] + 1] : m;
+        my_r2[lo[u] + ar[u]] = r2[u];
+        my_jt[lo[u] + ar[u]] = jt[u];
+      }
+    }
+    wave_sync();
+#pragma unroll
+    for (int u = 0; u < kNlPer; ++u) {
+      if (u >= nu) break;
+      int rank = lo[u];
+      for (int e = lo[u]; __ballot(e < hi[u]); ++e) {
+        if (e < hi[u]) {
+          const uint64_t o = my_r2[e];
+          // one type per bucket: (r2, j) decides
+          rank += o < r2[u] || (o == r2[u] && my_jt[e] < jt[u]) ? 1 : 0;
+        }
+      }
+      int to = rank, end = g.sel[0];       // the slot, and the end of its block
+      if constexpr (!kOne) {
+        const int t = (int)(jt[u] >> kJBits);
+        for (int v = 0; v < ntypes; ++v) {
+          const int shift_v = g.blk[v] - __builtin_amdgcn_readlane(firstv, v);
+          to = v == t ? rank + shift_v : to;
+          end = v == t ? g.blk[v + 1] : end;
+        }
+      }
+      if (64 * u + lane < m && to < end) row[to] = (int)(jt[u] & kJMask);
+    }
+  }
+  // lists that did not fit: one wavefront after the other, in all of the LDS
+  if (lane == 0) longer[wave] = m > kNlKeep;
+  __syncthreads();
+  for (int w = 0; w < kNlWaves; ++w) {
+    if (!longer[w]) continue;              // the same for every thread
+    __syncthreads();
+    if (w != wave) continue;
+    my_r2 = cand_r2;
+    my_jt = cand_jt;
+    collect(kNlCap);
+    int cnt[DPC_MAX_TYPES];
+#pragma unroll
+    for (int t = 0; t < DPC_MAX_TYPES; ++t) cnt[t] = 0;
+    // four entries that rank after every neighbour (type field 15) after the
+    // kept ones, so that the ranking below reads the list four at a time
+    if (lane < 4) {
+      my_r2[m + lane] = ~0ull;
+      my_jt[m + lane] = ~0u;
+    }
+    wave_sync();
+    for (int b = 0; b < m; b += 64) {
+      const int q = b + lane;
+      const int ty = q < m ? (int)(my_jt[q] >> kJBits) : -1;
+#pragma unroll
+      for (int t = 0; t < DPC_MAX_TYPES; ++t) cnt[t] += __popcll(ballot(ty == t));
+    }
+    // slot of each kept neighbour: its rank among the neighbours of its type
+    // by (r2, j), i.e. its rank among all of them by (type, r2, j) less the
+    // number of neighbours of smaller types; up to four candidates per lane
+    // per pass over all m, four list entries per step
+    for (int b = 0; b < m; b += 256) {
+      uint64_t own_r2[4];
+      uint32_t own_jt[4];
+      unsigned rank[4];
+      const int nu = min(4, (m - b + 63) / 64);   // candidate sets of this pass
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int q = b + 64 * u + lane;
+        own_r2[u] = q < m ? my_r2[q] : ~0ull;
+        own_jt[u] = q < m ? my_jt[q] : ~0u;
+        rank[u] = 0;
+#pragma unroll
+        for (int t = 0; t < DPC_MAX_TYPES; ++t)
+          rank[u] -= (uint32_t)t < (own_jt[u] >> kJBits) ? (unsigned)cnt[t] : 0u;
+      }
+      for (int e = 0; e < m; e += 4) {
+        uint64_t o_r2[4];
+        uint32_t o_jt[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          o_r2[v] = my_r2[e + v];
+          o_jt[v] = my_jt[e + v];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (u >= nu) break;
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            rank[u] = count_before(o_r2[v], o_jt[v], own_jt[u] & kJMask, (uint32_t)own_r2[u],
+                                   (uint32_t)(own_r2[u] >> 32), own_jt[u] >> kJBits, rank[u]);
+        }
       }
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
-        if (u >= nu) break;
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-          rank[u] = count_before(o_r2[v], o_jt[v], own_jt[u] & kJMask, (uint32_t)own_r2[u],
-                                 (uint32_t)(own_r2[u] >> 32), own_jt[u] >> kJBits, rank[u]);
+        const int q = b + 64 * u + lane;
+        const int t = (int)(own_jt[u] >> kJBits);
+        if (q < m && (int)rank[u] < g.sel[t]) row[g.blk[t] + (int)rank[u]] = (int)(own_jt[u] & kJMask);
       }
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int q = b + 64 * u + lane;
-      const int t = (int)(own_jt[u] >> kJBits);
-      if (q < m && (int)rank[u] < g.sel[t]) row[g.blk[t] + (int)rank[u]] = (int)(own_jt[u] & kJMask);
-    }
+    for (int t = 0; t < DPC_MAX_TYPES; ++t) cntv = lane == t ? cnt[t] : cntv;
   }
+  if (!active) return;
   // empty slots of each block
-  for (int s = lane; s < g.nnei; s += 64) {
-    int t = 0;
-#pragma unroll
-    for (int u = 1; u < DPC_MAX_TYPES; ++u) t += (u < g.ntypes && s >= g.blk[u]) ? 1 : 0;
-    int c = 0;
-#pragma unroll
-    for (int u = 0; u < DPC_MAX_TYPES; ++u) c = u == t ? cnt[u] : c;
-    if (s - g.blk[t] >= c) row[s] = -1;
+  for (int t = 0; t < ntypes; ++t) {
+    const int end = g.blk[t + 1];
+    for (int s = g.blk[t] + __builtin_amdgcn_readlane(cntv, t) + lane; s < end; s += 64) row[s] = -1;
   }
-  if (lane == 0) {
-    bool trunc = false;
-#pragma unroll
-    for (int t = 0; t < DPC_MAX_TYPES; ++t) trunc |= t < g.ntypes && cnt[t] > g.sel[t];
-    if (trunc) atomicAdd(status, 1);
-    if (n > kNlCap) atomicAdd(status + 1, 1);
+  if (lane < DPC_MAX_TYPES) {
+    const bool trunc = lane < ntypes && cntv > g.blk[lane + 1] - g.blk[lane];
+    if (__ballot(trunc) && lane == 0) atomicAdd(status, 1);
+    if (n > kNlCap && lane == 0) atomicAdd(status + 1, 1);
   }
 }
 
@@ -386,6 +537,8 @@ int make_geo(int nloc, int ntypes, const int* sel, double box, double rc, NlGeo*
   g->rc2 = rc * rc;
   g->inv_cs = g->nc / box;
   g->inv_box = 1.0 / box;
+  g->type_buckets = 256 / ntypes;      // kNlBuckets shared out
+  g->bucket_scale = g->type_buckets / g->rc2;
   return DPC_OK;
 }
 
@@ -429,8 +582,9 @@ static int dpc_nlist_launch(void* stream, int nloc, int ntypes, const int* sel, 
   hipLaunchKernelGGL(nl_cell_kernel, ga, b256, 0, s, g, coord, count, cell_of);
   hipLaunchKernelGGL(nl_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, g.ncell, count, start, cursor);
   hipLaunchKernelGGL(nl_scatter_kernel, ga, b256, 0, s, g, coord, atype, cell_of, cursor, sorted);
-  hipLaunchKernelGGL(nl_list_kernel, dim3((nloc + kNlWaves - 1) / kNlWaves), dim3(64 * kNlWaves), 0, s,
-                     g, coord, cell_of, start, sorted, nlist, status);
+  hipLaunchKernelGGL(ntypes == 1 ? nl_list_kernel<true> : nl_list_kernel<false>,
+                     dim3((nloc + kNlWaves - 1) / kNlWaves), dim3(64 * kNlWaves), 0, s, g, coord, cell_of, start,
+                     sorted, nlist, status);
   const int ls = dpc_internal_launch_status();
   if (ls != DPC_OK || !status_host) return ls;
   int h[2] = {0, 0};
