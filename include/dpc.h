@@ -323,14 +323,16 @@ typedef struct {
 size_t dpc_fitting_workspace_bytes(int nloc, int width);
 
 /* E [nloc] and, if dE_dD is not NULL, dE/dD [nloc][n_in] (float64) for
- * D [nloc][n_in] (float64, device).  The layer products run as rocBLAS
+ * D [nloc][n_in] (float64, device).  For width 240, n_in a multiple of 4 and
+ * 16-byte aligned D, dE_dD, weights and biases the products run in the
+ * library's own kernels on the float64 matrix cores; else as rocBLAS
  * double-precision GEMMs on the caller's handle `blas` (a rocblas_handle as
- * void*; its stream is left set to `stream`; its pointer mode is host for
- * the call and restored after it);
+ * void*, required in both cases; its stream is left set to `stream`; its
+ * pointer mode is host for the call and restored after it);
  * this library allocates nothing: `workspace` (device, 16-byte aligned,
  * >= dpc_fitting_workspace_bytes) is the caller's (rocBLAS may keep a
  * workspace of its own inside the handle).  Sums have a fixed order
- * for a given rocBLAS.  DPC_EHIP reports a HIP or rocBLAS failure.          */
+ * (for a given rocBLAS).  DPC_EHIP reports a HIP or rocBLAS failure.        */
 int dpc_fitting_fwd_bwd(void* stream, void* blas, int nloc, const dpc_fitting_net* net,
                         const double* D, void* workspace, size_t workspace_bytes, double* E,
                         double* dE_dD);
