@@ -109,6 +109,9 @@ __device__ __forceinline__ const Rec<TI>& zrec(const unsigned char* lds, uint32_
       __builtin_assume_aligned(lds + zoff + (uint32_t)e * (uint32_t)sizeof(Rec<TI>), 16));
 }
 
+template <typename TA>
+using Pair = TA __attribute__((ext_vector_type(2)));
+
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
 
@@ -143,6 +146,10 @@ __device__ __forceinline__ void locate(const PairRange& P, double x, int& l, dou
     t = P.d2;
   }
 }
+
+// A record that the forward's moments of the first interval may take (t^5
+// stays far from overflow).
+__device__ __forceinline__ bool first_interval(int l, double t) { return l == 0 && fabs(t) < 1e8; }
 
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -414,7 +421,8 @@ __device__ __forceinline__ Tables build_chunk_set(const Geo& g, const int (&ai)[
                                                   const TI* __restrict__ em, Rec<TI>* z,
                                                   ChunkScratch& W, int lane,
                                                   int* pair = nullptr, Rec<TI>* mine = nullptr,
-                                                  bool use_pre = false, const TI* pre = nullptr) {
+                                                  bool use_pre = false, const TI* pre = nullptr,
+                                                  bool drop_first = false) {
   constexpr int kC = kLanes / NB;
   const int a = lane / kC, sl = lane % kC, j = s0 + sl;
   int at = -1;
@@ -452,6 +460,7 @@ __device__ __forceinline__ Tables build_chunk_set(const Geo& g, const int (&ai)[
       locate(P, (double)rec.r[0], l, rec.t, cl);
       rec.pad = 0.0;
       key = (blk << kOffBits) | (kOffMask - (P.offset + l * 6 * g.ld));
+      if (drop_first && first_interval(l, rec.t)) valid = false;
       // beyond the table the derivative term vanishes: a zero row removes it
       // (a NaN or infinite x keeps its row, so that it propagates)
       if (kBwd && cl && isfinite(rec.r[0])) {
@@ -554,6 +563,10 @@ __device__ __forceinline__ Tables build_chunk_set(const Geo& g, const int (&ai)[
   return T;
 }
 
+__device__ __forceinline__ double mfma4(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
 // ---------------------------------------------------------------------------
 // forward: T and D
 // ---------------------------------------------------------------------------
@@ -565,8 +578,115 @@ __host__ __device__ constexpr size_t fwd_wave_bytes(int m1) {
              : align16((size_t)m1 * 4 * sizeof(TA));
 }
 
-template <typename TA>
-using Pair = TA __attribute__((ext_vector_type(2)));
+// The records of the first interval of each table, whole: s(r) leaves zero
+// with zero slope, so the neighbours near the cutoff crowd into it (17% of all
+// records in water, 22% in Cu with r_c 8, 31% in Al-Cu-Mg), and
+//   sum_j g_m(t_j) R~_j[k] = sum_q C[m][q] Q[q][k],  Q[q][k] = sum_j t_j^q R~_j[k]
+// costs 24 multiply-adds per channel however many they are, not 9 for each.
+// Q of the wavefront's four atoms comes from the matrix cores (v_mfma_f64_4x4x4:
+// block = atom, row = power, column = k, K = four of the atom's 16 slots), two
+// accumulators per lane.  Lists sorted by distance hold these records at the
+// end of a block's valid slots: chunk sets that lie inside a block are taken
+// from its last occupied one backwards while they hold at least kTakeMin such
+// records.  In other orders fewer are found; what is not taken here goes
+// through the runs like every other record.  A look at a chunk set is a chain
+// of waits (row, interval, LDS), so only blocks of at least kTakeLen slots are
+// looked at.  Forward, us before and after (float64, M1 = 100): Cu r_c 8,
+// 1,048,576 atoms 16,430 / 15,700, 131,072: 2,190 / 2,090; Cu r_c 6, M1 = 128,
+// float32, 55,296 atoms: 437 / 403; with water's blocks of 46 and 92 slots
+// taken too, 192,000 atoms lost 4%.  Returns the chunk sets taken; `occ` loses
+// those that held nothing else.
+constexpr int kTakeMin = 12, kTakeLen = 128;
+
+template <typename TI, typename TA, int CPL, bool kOne>
+__device__ __forceinline__ uint32_t first_interval_moments(
+    const Geo& g, const WaveAtoms<4>& wa, const int (&ai)[4], int atom, uint32_t vm, uint32_t& occ,
+    const TI* __restrict__ em, WaveLds<TI>& W, __amdgpu_buffer_rsrc_t rs, int ld, int voff, bool active,
+    int lane, TI (&cf)[6][CPL], TA (&acc)[4][CPL][4]) {
+  constexpr int NB = 4, kC = kLanes / NB;
+  const int a = lane / kC, sl = lane % kC;
+  int at = -1;
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+    if (b == a) at = ai[b];
+  const int kk = lane >> 4, blk4 = (lane >> 2) & 3, x = lane & 3;   // place in the products
+  const int nch = (g.nnei + kC - 1) / kC;
+  uint32_t taken = 0;
+  for (int beta = 0; beta < (kOne ? 1 : g.ntypes); ++beta) {
+    // chunk sets inside the block
+    const int c0 = kOne || beta == 0 ? 0 : (g.blk_end[beta - 1] + kC - 1) / kC;
+    const int c1 = kOne || beta == g.ntypes - 1 ? nch : g.blk_end[beta] / kC;
+    const int len = g.blk_end[beta] - (beta == 0 ? 0 : g.blk_end[beta - 1]);
+    if (c0 >= c1 || len < kTakeLen) continue;
+    uint32_t bits = occ & ((c1 >= 32 ? 0u : 1u << c1) - 1u) & ~((1u << c0) - 1u);
+    const PairRange P = g.pr[kOne || at < 0 ? 0 : at * g.ntypes + beta];
+    double q03 = 0.0, q45 = 0.0;             // lane (i, b, j): Q[i][j] and Q[4 + i][j] of atom b
+    bool any = false;
+    while (bits) {
+      const int c = 31 - __builtin_clz(bits);
+      bits &= ~(1u << c);
+      const int j = c * kC + sl, il = a * (kWindow / NB) + j;
+      const int holder = __builtin_amdgcn_ds_bpermute((il & 63) << 2, (int)vm);
+      const bool valid = at >= 0 && j < g.nnei && ((holder >> (il >> 6)) & 1);
+      TI r[4] = {(TI)0, (TI)0, (TI)0, (TI)0};
+      double t = 0.0;
+      bool hit = false;
+      if (valid) {
+        load_row(em + ((size_t)atom * g.nnei + j) * 4, r);
+        int l;
+        bool cl;
+        locate(P, (double)r[0], l, t, cl);
+        hit = first_interval(l, t);
+      }
+      const uint64_t mh = __ballot(hit);
+      if (__popcll(mh) < kTakeMin) break;
+      taken |= 1u << c;
+      if (mh == __ballot(valid)) occ &= ~(1u << c);
+      any = true;
+      Rec<TI>& z = W.z[lane];
+      z.t = hit ? t : 0.0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) z.r[k] = hit ? r[k] : (TI)0;
+      wave_sync();
+#pragma unroll
+      for (int s = 0; s < kC / 4; ++s) {
+        const Rec<TI>& e = W.z[kC * blk4 + 4 * s + kk];
+        const double u = e.t, u2 = u * u, v = (double)e.r[x];
+        const double p = (x & 1 ? u : 1.0) * (x & 2 ? u2 : 1.0);   // t^x
+        q03 = mfma4(p, v, q03);
+        q45 = mfma4(p * (u2 * u2), v, q45);
+      }
+      wave_sync();
+    }
+    if (!any) continue;
+    double* sq = reinterpret_cast<double*>(W.z);       // [atom][power][k]
+    sq[blk4 * 24 + kk * 4 + x] = q03;
+    if (kk < 2) sq[blk4 * 24 + 16 + kk * 4 + x] = q45;
+    wave_sync();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      if (ai[b] < 0) continue;
+      if (!kOne || b == 0)
+        load_coef<TI, CPL>(rs, g.pr[kOne ? 0 : ai[b] * g.ntypes + beta].offset, ld, voff, cf);
+      if (!active) continue;
+#pragma unroll
+      for (int q = 0; q < 6; ++q) {
+        const Pair<double>* row = reinterpret_cast<const Pair<double>*>(sq + b * 24 + q * 4);
+        const Pair<double> v01 = row[0], v23 = row[1];
+#pragma unroll
+        for (int h = 0; h < CPL; ++h) {
+          const double c = (double)cf[q][h];
+          acc[b][h][0] = (TA)fma(c, v01.x, (double)acc[b][h][0]);
+          acc[b][h][1] = (TA)fma(c, v01.y, (double)acc[b][h][1]);
+          acc[b][h][2] = (TA)fma(c, v23.x, (double)acc[b][h][2]);
+          acc[b][h][3] = (TA)fma(c, v23.y, (double)acc[b][h][3]);
+        }
+      }
+    }
+    wave_sync();
+  }
+  return taken;
+}
 
 // kOne: all atoms and neighbours have one type (one table, no blocks)
 template <typename TI, typename TA, int CPL, int NB, bool kOne, int kSplit = 1>
@@ -636,8 +756,18 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
   const int nch = (nnei + kC - 1) / kC;
   int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
-  int turn = 0;
-  for (int cc = 0, wbase = -1; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
+  int turn = 0, wbase = -1;
+  uint32_t taken = 0;          // chunk sets whose first-interval records the moments have taken
+  if constexpr (NB == 4 && !kShared) {
+    if (nnei <= kWindow / NB) {
+      wbase = 0;
+      vm = valid_window<NB>(g, wa, 0, nlist, lane);
+      occ = occupied_chunks<NB>(vm);
+      taken = first_interval_moments<TI, TA, CPL, kOne>(g, wa, ai, my_atom, vm, occ, em, W, rs, ld, voff, active,
+                                                        lane, cfA, acc);
+    }
+  }
+  for (int cc = 0; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
     if (s0 - s0 % (kWindow / NB) != wbase) {  // window of nlist signs holding s0
       wbase = s0 - s0 % (kWindow / NB);
       vm = valid_window<NB>(g, wa, wbase, nlist, lane);
@@ -645,7 +775,9 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
     }
     if (!((occ >> ((s0 - wbase) / kC)) & 1)) continue;   // padding only
     if (kShared && NB > 1 && turn++ % kSplit != wave) continue;
-    const Tables tb = build_chunk_set<TI, TA, NB, false, kOne>(g, ai, my_atom, s0, wbase, vm, em, W.z, W.s, lane);
+    const Tables tb = build_chunk_set<TI, TA, NB, false, kOne>(g, ai, my_atom, s0, wbase, vm, em, W.z, W.s, lane,
+                                                              nullptr, nullptr, false, nullptr,
+                                                              (taken >> ((s0 - wbase) / kC)) & 1);
     if (tb.n == 0) continue;
     int r = 0, r1 = tb.nruns;
     if constexpr (kShared && NB == 1) {
@@ -1074,10 +1206,6 @@ __host__ __device__ constexpr int pair_slots(int ns, int nb = kMfmaAtoms) {
 __host__ __device__ constexpr size_t bwdm_wave_bytes(int ns, int nb = kMfmaAtoms) {
   return align16(sizeof(ChunkScratch)) + (size_t)pair_slots(ns, nb) * kPairDoubles * sizeof(double) +
          (size_t)1024 * ns;
-}
-
-__device__ __forceinline__ double mfma4(double a, double b, double c) {
-  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
 
 // v from lane l - N of the same row of 16 lanes (0 for the first N lanes)
