@@ -157,8 +157,8 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The NB atoms of a wavefront.  A workgroup takes kWaves * NB consecutive
-// atoms.  With several types it hands them to its wavefronts grouped by type
+// The NB atoms of a wavefront (of group `wave` of kGroups).  A workgroup takes
+// kGroups * NB consecutive atoms.  With several types it hands them to its wavefronts grouped by type
 // (atoms of an invalid type after the others, index order inside a group),
 // so that the atoms of one wavefront share their tables as often as
 // possible: more records per interval.  An atom's records and sums do not
@@ -174,10 +174,10 @@ struct WaveAtoms {
   int lanes;
 };
 
-template <int NB, bool kOne>
+template <int NB, bool kOne, int kGroups = kWaves>
 __device__ __forceinline__ WaveAtoms<NB> wave_atoms(const Geo& g, const int* __restrict__ atype,
                                                     int lane, int wave) {
-  constexpr int kG = kWaves * NB;
+  constexpr int kG = kGroups * NB;
   static_assert(kG <= kLanes, "one lane per atom of the workgroup");
   WaveAtoms<NB> w;
   const int base = (int)blockIdx.x * kG;
@@ -689,7 +689,14 @@ __device__ __forceinline__ uint32_t first_interval_moments(
 }
 
 // kOne: all atoms and neighbours have one type (one table, no blocks)
-template <typename TI, typename TA, int CPL, int NB, bool kOne, int kSplit = 1>
+// kHalves = 2 (float64, more than 128 channels): two wavefronts serve the same
+// atoms, the second one the channels from 128 on, so that each keeps to the
+// registers of 128 channels and three share a SIMD (four channels per lane
+// leave one).  Cu r_c 6, M1 = 200, 8,788 atoms: 309 us with four channels per
+// lane, 205 so.  Float32 coefficients leave two and three wavefronts per SIMD
+// also with four channels per lane (mixed, M1 = 256, 32,000 Al-Cu-Mg atoms:
+// 820 us, 905 with halves), so those modes keep them.
+template <typename TI, typename TA, int CPL, int NB, bool kOne, int kSplit = 1, int kHalves = 1>
 // up to 128 channels: registers capped so that 3 wavefronts fit on a SIMD
 __global__ __launch_bounds__(64 * (kSplit > 1 ? kSplit : kWaves))
 __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
@@ -702,19 +709,23 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
   const int wave = threadIdx.x >> 6;
   constexpr bool kShared = kSplit > 1;
   WaveAtoms<NB> wa;
+  static_assert(kHalves == 1 || !kShared, "halves of the channels, or shared atoms");
+  const int half = kHalves > 1 ? wave % kHalves : 0;
   if constexpr (kShared) wa = shared_atoms<NB>(g, lane);
-  else wa = wave_atoms<NB, kOne>(g, atype, lane, wave);
-  if (wa.idx[0] < 0) return;
+  else wa = wave_atoms<NB, kOne, kWaves / kHalves>(g, atype, lane, wave / kHalves);
+  // (halves meet at barriers: wavefronts without atoms stay)
+  if (kHalves == 1 && wa.idx[0] < 0) return;
   // the threads that write an atom's outputs together
-  constexpr int kOut = kShared ? 64 * kSplit : 64;
-  const int tid = kShared ? (int)threadIdx.x : lane;
+  constexpr int kOut = kShared ? 64 * kSplit : 64 * kHalves;
+  const int tid = kShared ? (int)threadIdx.x : half * 64 + lane;
+  const int ch0 = half * 64 * CPL + lane * CPL;          // the lane's first channel
   const int my_atom = lane_atom_of<NB>(wa, lane / kC);   // the atom of this lane's chunk-set slots
   const int nnei = g.nnei, m1 = g.m1, m2 = g.m2, ld = g.ld;
   const uint32_t zoff = __builtin_amdgcn_readfirstlane(wave * (uint32_t)fwd_wave_bytes<TI, TA>(m1));
   unsigned char* wb = smem + zoff;
   WaveLds<TI>& W = *reinterpret_cast<WaveLds<TI>*>(wb);
   const __amdgpu_buffer_rsrc_t rs = make_rsrc(coeff, g.coeff_bytes);
-  const int voff = 2 * min(lane * CPL, ld - CPL) * (int)sizeof(TI);
+  const int voff = 2 * min(ch0, ld - CPL) * (int)sizeof(TI);
 
   int ai[NB];
 #pragma unroll
@@ -746,7 +757,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
   // others, so that every load stays unconditional, but skip the arithmetic:
   // idle float64 FMAs still draw power, and this kernel runs at a lower
   // clock than the rest
-  const bool active = lane * CPL < m1;
+  const bool active = ch0 < m1;
 
   // Chunk sets are visited cyclically from a start that differs between
   // wavefronts, so that waves sharing a SIMD are not all building (a
@@ -759,7 +770,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
   int turn = 0, wbase = -1;
   uint32_t taken = 0;          // chunk sets whose first-interval records the moments have taken
   if constexpr (NB == 4 && !kShared) {
-    if (nnei <= kWindow / NB) {
+    if (wa.idx[0] >= 0 && nnei <= kWindow / NB) {
       wbase = 0;
       vm = valid_window<NB>(g, wa, 0, nlist, lane);
       occ = occupied_chunks<NB>(vm);
@@ -767,7 +778,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
                                                         lane, cfA, acc);
     }
   }
-  for (int cc = 0; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
+  for (int cc = kHalves > 1 && wa.idx[0] < 0 ? nch : 0; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
     if (s0 - s0 % (kWindow / NB) != wbase) {  // window of nlist signs holding s0
       wbase = s0 - s0 % (kWindow / NB);
       vm = valid_window<NB>(g, wa, wbase, nlist, lane);
@@ -841,21 +852,21 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
   // Wavefronts that share their atoms add their partial rows first, in
   // wavefront order, into the first one's LDS.
   auto sync = [&]() __attribute__((always_inline)) {
-    if constexpr (kShared) __syncthreads();
+    if constexpr (kShared || kHalves > 1) __syncthreads();
     else wave_sync();
   };
-  TA* sT = reinterpret_cast<TA*>(kShared ? smem : wb);
+  TA* sT = reinterpret_cast<TA*>(kShared ? smem : wb - half * fwd_wave_bytes<TI, TA>(m1));
   const int m_step = kOut / m2, n_step = kOut % m2;
 #pragma unroll
   for (int a = 0; a < NB; ++a) {
     const int i = wa.idx[a];
-    if (ai[a] < 0) continue;
+    if (kHalves == 1 && ai[a] < 0) continue;
     sync();
 #pragma unroll
     for (int h = 0; h < CPL; ++h) {
-      const int m = lane * CPL + h;
+      const int m = ch0 + h;
       if (m < m1) {
-        Pair<TA>* d = reinterpret_cast<Pair<TA>*>(reinterpret_cast<TA*>(wb) + m * 4);
+        Pair<TA>* d = reinterpret_cast<Pair<TA>*>((kShared ? reinterpret_cast<TA*>(wb) : sT) + m * 4);
         d[0] = Pair<TA>{acc[a][h][0], acc[a][h][1]};
         d[1] = Pair<TA>{acc[a][h][2], acc[a][h][3]};
       }
@@ -871,6 +882,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
       }
       sync();
     }
+    if (kHalves > 1 && ai[a] < 0) continue;
     TA* Ti = T + (size_t)i * m1 * 4;
     TA* Di = D + (size_t)i * m1 * m2;
     auto dot = [&](int m, int n) __attribute__((always_inline)) -> TA {
@@ -1146,7 +1158,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// backward, float64, M1 <= 128: channel sums on the matrix cores
+// backward, float64 sums: channel sums on the matrix cores
 // ---------------------------------------------------------------------------
 // For one interval (coefficients C[m][q], g_m(t) = sum_q C[m][q] t^q) and
 // one atom (dE/dT rows dT[m][k]) both channel sums of a record factor
@@ -1190,21 +1202,20 @@ __host__ __device__ constexpr int mfma_slot_kib(int S, int ld, int esize = 8) {
 
 // The (interval, atom) products are stored as rows of 6 doubles, 26 doubles
 // (13 bank groups) apart, so that the records of up to 16 different products
-// read without conflicts; pair_slots of them are held at once.  Four
-// wavefronts' LDS stays at or below 53,312 bytes, so that three workgroups
-// share a CU (measured: 53,824 bytes leave room for two).
+// read without conflicts; pair_slots of them are held at once.  Up to 128
+// channels four wavefronts' LDS stays at or below 53,312 bytes, so that three
+// workgroups share a CU (measured: 53,824 bytes leave room for two); above,
+// the registers leave room for two, of 64 KiB each.
 constexpr int kPairDoubles = 26;   // one product in LDS: 4 rows of 6 + 2 padding
-constexpr int kMfmaWaveLds = 53312 / kWaves;
-__host__ __device__ constexpr int pair_slots(int ns, int nb = kMfmaAtoms) {
-  // a wavefront that serves one atom holds few products at a time
-  return nb == 1 ? 8 : ((kMfmaWaveLds - (int)align16(sizeof(ChunkScratch)) - 1024 * ns) /
-              (kPairDoubles * (int)sizeof(double)) / 4 * 4 > 32
-              ? 32
-              : (kMfmaWaveLds - (int)align16(sizeof(ChunkScratch)) - 1024 * ns) /
-                    (kPairDoubles * (int)sizeof(double)) / 4 * 4);
+constexpr int kMfmaWide = 8;       // K steps up to which three wavefronts share a SIMD
+__host__ __device__ constexpr int pair_slots(int S, int ns, int nb = kMfmaAtoms) {
+  const int wave_lds = (S <= kMfmaWide ? 53312 : 65536) / kWaves;
+  const int fit = (wave_lds - (int)align16(sizeof(ChunkScratch)) - 1024 * ns) /
+                  (kPairDoubles * (int)sizeof(double)) / 4 * 4;
+  return nb == 1 ? 8 : (fit > 32 ? 32 : fit);   // one atom's wavefront holds few products at a time
 }
-__host__ __device__ constexpr size_t bwdm_wave_bytes(int ns, int nb = kMfmaAtoms) {
-  return align16(sizeof(ChunkScratch)) + (size_t)pair_slots(ns, nb) * kPairDoubles * sizeof(double) +
+__host__ __device__ constexpr size_t bwdm_wave_bytes(int S, int ns, int nb = kMfmaAtoms) {
+  return align16(sizeof(ChunkScratch)) + (size_t)pair_slots(S, ns, nb) * kPairDoubles * sizeof(double) +
          (size_t)1024 * ns;
 }
 
@@ -1327,7 +1338,6 @@ __device__ __forceinline__ void wait_copies() {
   __asm__ __volatile__("" ::: "memory");
 }
 
-// up to 128 channels: registers capped so that 3 wavefronts fit on a SIMD
 // The A operands of the wavefront's NB atoms from T and dE/dD (the
 // descriptor backward), on the matrix cores.  Both sums are 4 x 4 x 4
 // products whose output layout is the A operand layout itself: output lane
@@ -1450,15 +1460,19 @@ __device__ __forceinline__ void descriptor_bwd_operands_shared(const Geo& g, con
 //   dE/dT[m][k] = sum_{n<M'} dE/dD[m][n] T[n][k] + (m < M') sum_m' dE/dD[m'][m] T[m'][k],
 // evaluated per atom on the matrix cores straight into the A operands, so
 // dE/dT never goes to memory.
+// Up to 128 channels registers are capped so that 3 wavefronts fit on a SIMD,
+// above so that 2 do (dE/dT of four atoms takes up to 128 registers there; the
+// vector kernel that served those widths took 320 us on 8,788 atoms at M1 =
+// 200, 496 on 6,912 Al-Cu-Mg atoms at 256; this one takes 236 and 372).
 template <typename TI, typename TO, int S, int NS, bool kOne, bool kFromD = false,
           int NB = kMfmaAtoms, int kSplit = 1>
-__global__ __launch_bounds__(64 * (kSplit > 1 ? kSplit : kWaves)) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(64 * (kSplit > 1 ? kSplit : kWaves)) __attribute__((amdgpu_waves_per_eu(S <= kMfmaWide ? 3 : 2)))
 void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
                           const int* __restrict__ atype, const int* __restrict__ nlist,
                           const TI* __restrict__ em, const TI* __restrict__ dT,
                           TO* __restrict__ dR, const double* __restrict__ Tin = nullptr,
                           const double* __restrict__ dD = nullptr) {
-  static_assert(S >= 1 && S <= 8, "K steps per channel block");
+  static_assert(S >= 1 && S <= 16, "K steps per channel block");
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr bool kShared = kSplit > 1;
   constexpr int kC = kLanes / NB;
@@ -1470,8 +1484,8 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
   if (wa.idx[0] < 0) return;
   const int my_atom = lane_atom_of<NB>(wa, lane / kC);   // the atom of this lane's chunk-set slots
   const int nnei = g.nnei, m1 = g.m1, ld = g.ld;
-  constexpr int kPairSlots = pair_slots(NS, NB);
-  const uint32_t zoff = __builtin_amdgcn_readfirstlane(wave * (uint32_t)bwdm_wave_bytes(NS, NB));
+  constexpr int kPairSlots = pair_slots(S, NS, NB);
+  const uint32_t zoff = __builtin_amdgcn_readfirstlane(wave * (uint32_t)bwdm_wave_bytes(S, NS, NB));
   ChunkScratch& W = *reinterpret_cast<ChunkScratch*>(smem + zoff);
   const uint32_t store = lds_addr(smem) + zoff + (uint32_t)align16(sizeof(ChunkScratch));
   unsigned char* const slot_p =
@@ -1494,7 +1508,7 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
     descriptor_bwd_operands_shared<NB, S, kSplit>(g, wa, Tin, dD, lane, wave, reinterpret_cast<double*>(smem), A);
   else if constexpr (kFromD)
     descriptor_bwd_operands<NB, S>(g, wa, Tin, dD, lane, A);
-  static_assert(!kShared || (NB * S + kSplit) * kLanes * sizeof(double) <= kSplit * bwdm_wave_bytes(NS, NB),
+  static_assert(!kShared || (NB * S + kSplit) * kLanes * sizeof(double) <= kSplit * bwdm_wave_bytes(S, NS, NB),
                 "the shared operands fit in the workgroup's LDS");
 #pragma unroll
   for (int a = 0; a < NB; ++a) {
@@ -1609,22 +1623,25 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
       auto run = [&](int r, auto last) __attribute__((always_inline)) {
         constexpr bool kLast = decltype(last)::value;
         wait_copies();
+        constexpr int kS1 = S < 8 ? S : 8, kS2 = S > 8 ? S - 8 : 1;   // one read block, or two
         double Bc[2][S];
         if constexpr (sizeof(TI) == 8) {
-          v4i q[S];
-          lds_read_steps<S>(bread, q);
+          v4i q[kS1], q2[kS2];
+          lds_read_steps<kS1>(bread, q);
+          if constexpr (S > 8) lds_read_steps<kS2>(bread + 8 * 256, q2);
 #pragma unroll
           for (int st = 0; st < S; ++st) {
-            const Pair<double> v = __builtin_bit_cast(Pair<double>, q[st]);
+            const Pair<double> v = __builtin_bit_cast(Pair<double>, st < 8 ? q[st < kS1 ? st : 0] : q2[st >= 8 && st - 8 < kS2 ? st - 8 : 0]);
             Bc[0][st] = v.x;
             Bc[1][st] = v.y;
           }
         } else {
-          v2i q[S];
-          lds_read_steps_b64<S>(bread, q);
+          v2i q[kS1], q2[kS2];
+          lds_read_steps_b64<kS1>(bread, q);
+          if constexpr (S > 8) lds_read_steps_b64<kS2>(bread + 8 * 128, q2);
 #pragma unroll
           for (int st = 0; st < S; ++st) {
-            const Pair<float> v = __builtin_bit_cast(Pair<float>, q[st]);
+            const Pair<float> v = __builtin_bit_cast(Pair<float>, st < 8 ? q[st < kS1 ? st : 0] : q2[st >= 8 && st - 8 < kS2 ? st - 8 : 0]);
             Bc[0][st] = (double)v.x;
             Bc[1][st] = (double)v.y;
           }
@@ -1752,7 +1769,7 @@ int make_geo(int nloc, int ntypes, const int* sel, int m1, int m2, const dpc_ran
 //   forward    256: 67 / 33 / 16    1,372: 70 / 38 / 37    4,000: 76 / 73 / 87    6,912: 90 / 109 / 146
 //   matrix bwd 256: 69 / 32 / 16    1,372: 72 / 39 / 35    4,000: 77 / 76 / 85    6,912: 104 / 112 / 142
 //   vector bwd (float32) 256: 48 / 25 / 16    864: 50 / 29 / 30    1,372: 51 / 33 / 34    2,048: 52 / 52 / 47
-//   forward, M1 = 200    500: 100 / 47 / 35    864: 103 / 47 / 64    2,048: 106 / 92 / 129    4,000: 117 / 177 / 250
+//   forward, M1 = 200    500: 69 / 47 / 36    864: 75 / 48 / 67    1,372: 83 / 92 / 101
 // (lists of 77 neighbours; with 180, kBySet wins up to about 10,000 atoms).
 enum class Split { kNone, kBySet, kByRun };
 Split split_of(int nloc, int run_max, int set_max) {
@@ -1762,11 +1779,11 @@ Split split_of(int nloc, int run_max, int set_max) {
 // Channels per lane: 1 (m1 <= 64), 2 (m1 <= 128) or 4 (m1 <= 256).
 int channels_per_lane(int m1) { return m1 <= 64 ? 1 : (m1 <= 128 ? 2 : 4); }
 
-template <typename TI, typename TA, int NB, int kSplit>
+template <typename TI, typename TA, int NB, int kSplit, int kHalves = 1>
 int launch_fwd_split(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
                      const void* em, void* T, void* D) {
   static_assert(NB == 1 || NB == 2 || NB == 4 || NB == 8, "atoms per wave: 1, 2, 4 or 8");
-  constexpr int waves = kSplit > 1 ? kSplit : kWaves, atoms = kSplit > 1 ? NB : kWaves * NB;
+  constexpr int waves = kSplit > 1 ? kSplit : kWaves, atoms = kSplit > 1 ? NB : kWaves / kHalves * NB;
   const dim3 grid((g.nloc + atoms - 1) / atoms), block(64 * waves);
   const size_t shm = waves * fwd_wave_bytes<TI, TA>(g.m1);
   if (shm > kMaxLds) return DPC_ENOTSUP;
@@ -1775,10 +1792,19 @@ int launch_fwd_split(hipStream_t s, const Geo& g, const void* coeff, const int* 
     hipLaunchKernelGGL(kern, grid, block, shm, s, g, (const TI*)coeff, atype, nlist,
                        (const TI*)em, (TA*)T, (TA*)D);
   };
-  switch (channels_per_lane(g.m1)) {
-    case 1: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 1, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 1, NB, false, kSplit>); break;
-    case 2: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 2, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 2, NB, false, kSplit>); break;
-    default: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 4, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 4, NB, false, kSplit>); break;
+  if constexpr (kHalves > 1) {
+    g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 2, NB, true, 1, 2>) : go(se_a_fwd_kernel<TI, TA, 2, NB, false, 1, 2>);
+  } else {
+    switch (channels_per_lane(g.m1)) {
+      case 1: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 1, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 1, NB, false, kSplit>); break;
+      case 2: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 2, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 2, NB, false, kSplit>); break;
+      default:
+        // (float64: four channels per lane only where wavefronts share atoms)
+        if constexpr (kSplit > 1 || sizeof(TI) == 4) {
+          g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 4, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 4, NB, false, kSplit>);
+        }
+        break;
+    }
   }
   return launch_status();
 }
@@ -1786,22 +1812,30 @@ int launch_fwd_split(hipStream_t s, const Geo& g, const void* coeff, const int* 
 template <typename TI, typename TA>
 int launch_fwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
                const void* em, void* T, void* D) {
-  // four channels per lane leave one wavefront per SIMD: half as many fit at once or fewer
-  switch (g.m1 <= 128 ? split_of(g.nloc, 1280, 6144) : split_of(g.nloc, 512, 2048)) {
+  // more than 128 channels: fewer wavefronts fit at once with four channels per lane
+  switch (g.m1 <= 128 ? split_of(g.nloc, 1280, 6144) : split_of(g.nloc, 512, sizeof(TI) == 8 ? 1024 : 2048)) {
     case Split::kByRun: return launch_fwd_split<TI, TA, 1, 8>(s, g, coeff, atype, nlist, em, T, D);
     case Split::kBySet: return launch_fwd_split<TI, TA, DPC_FWD_ATOMS_PER_WAVE, 4>(s, g, coeff, atype, nlist, em, T, D);
-    default: return launch_fwd_split<TI, TA, DPC_FWD_ATOMS_PER_WAVE, 1>(s, g, coeff, atype, nlist, em, T, D);
+    default:
+      if constexpr (sizeof(TI) == 8) {
+        if (g.m1 > 128)
+          return launch_fwd_split<TI, TA, DPC_FWD_ATOMS_PER_WAVE, 1, 2>(s, g, coeff, atype, nlist, em, T, D);
+      }
+      return launch_fwd_split<TI, TA, DPC_FWD_ATOMS_PER_WAVE, 1>(s, g, coeff, atype, nlist, em, T, D);
   }
 }
 
-// M1 <= 128, float64 or mixed: the matrix-core kernel, ceil(M1 / 16) K steps
+// float64 or mixed: the matrix-core kernel, ceil(M1 / 16) K steps
 // per channel block, an interval copied by mfma_slot_kib(S, ld, esize) loads
 // (ld lies in [16 S - 12, 16 S], so that count takes one of two values per S)
 template <typename TI, typename TO, int S, bool kFromD, int NB, int kSplit>
-void launch_mfma_s(hipStream_t s, const Geo& g, dim3 grid, dim3 block, const void* coeff,
+void launch_mfma_s(hipStream_t s, const Geo& g, dim3 grid, const void* coeff,
                    const int* atype, const int* nlist, const void* em, const void* dT, void* dR,
                    const double* Tin, const double* dD) {
   constexpr int es = (int)sizeof(TI);
+  // above 128 channels the LDS of eight wavefronts is too large for one workgroup
+  constexpr int split = S > kMfmaWide && kSplit > 4 ? 4 : kSplit;
+  const dim3 block(64 * (split > 1 ? split : kWaves));
   const int ns = mfma_slot_kib(S, g.ld, es);
   auto go = [&](auto kern, size_t wave_bytes) {
     hipLaunchKernelGGL(kern, grid, block, block.x / 64 * wave_bytes, s, g, (const TI*)coeff, atype,
@@ -1810,14 +1844,14 @@ void launch_mfma_s(hipStream_t s, const Geo& g, dim3 grid, dim3 block, const voi
   constexpr int lo = mfma_slot_kib(S, 16 * S - 12, es);
   static_assert(mfma_slot_kib(S, 16 * S, es) <= lo + 1, "two slot sizes per S");
   // (split workgroups always take the larger slot: latency, not LDS, limits them)
-  const bool small = kSplit == 1 && ns <= lo;
-  constexpr int hi = lo + 1, sm = kSplit == 1 ? lo : hi;
+  const bool small = split == 1 && ns <= lo;
+  constexpr int hi = lo + 1, sm = split == 1 ? lo : hi;
   if (g.ntypes == 1) {
-    if (small) go(se_a_bwd_mfma_kernel<TI, TO, S, sm, true, kFromD, NB, kSplit>, bwdm_wave_bytes(sm, NB));
-    else go(se_a_bwd_mfma_kernel<TI, TO, S, hi, true, kFromD, NB, kSplit>, bwdm_wave_bytes(hi, NB));
+    if (small) go(se_a_bwd_mfma_kernel<TI, TO, S, sm, true, kFromD, NB, split>, bwdm_wave_bytes(S, sm, NB));
+    else go(se_a_bwd_mfma_kernel<TI, TO, S, hi, true, kFromD, NB, split>, bwdm_wave_bytes(S, hi, NB));
   } else {
-    if (small) go(se_a_bwd_mfma_kernel<TI, TO, S, sm, false, kFromD, NB, kSplit>, bwdm_wave_bytes(sm, NB));
-    else go(se_a_bwd_mfma_kernel<TI, TO, S, hi, false, kFromD, NB, kSplit>, bwdm_wave_bytes(hi, NB));
+    if (small) go(se_a_bwd_mfma_kernel<TI, TO, S, sm, false, kFromD, NB, split>, bwdm_wave_bytes(S, sm, NB));
+    else go(se_a_bwd_mfma_kernel<TI, TO, S, hi, false, kFromD, NB, split>, bwdm_wave_bytes(S, hi, NB));
   }
 }
 
@@ -1826,17 +1860,22 @@ int launch_mfma_split(hipStream_t s, const Geo& g, const void* coeff, const int*
                       const int* nlist, const void* em, const void* dT, void* dR,
                       const double* Tin, const double* dD) {
   const int S = (g.m1 + 15) / 16;
-  constexpr int waves = kSplit > 1 ? kSplit : kWaves, atoms = kSplit > 1 ? NB : kWaves * NB;
-  const dim3 grid((g.nloc + atoms - 1) / atoms), block(64 * waves);
+  constexpr int atoms = kSplit > 1 ? NB : kWaves * NB;
+  const dim3 grid((g.nloc + atoms - 1) / atoms);
   (void)hipGetLastError();  // report only what this launch raises
-  switch (S) {
-#define DPC_CASE(n)                                                                                           \
-  case n:                                                                                                     \
-    launch_mfma_s<TI, TO, n, kFromD, NB, kSplit>(s, g, grid, block, coeff, atype, nlist, em, dT, dR, Tin, dD); \
+#define DPC_CASE(n)                                                                                   \
+  case n:                                                                                             \
+    launch_mfma_s<TI, TO, n, kFromD, NB, kSplit>(s, g, grid, coeff, atype, nlist, em, dT, dR, Tin, dD); \
     break;
+  switch (S) {
     DPC_CASE(1) DPC_CASE(2) DPC_CASE(3) DPC_CASE(4) DPC_CASE(5) DPC_CASE(6) DPC_CASE(7) DPC_CASE(8)
-#undef DPC_CASE
   }
+  if constexpr (!kFromD) {
+    switch (S) {
+      DPC_CASE(9) DPC_CASE(10) DPC_CASE(11) DPC_CASE(12) DPC_CASE(13) DPC_CASE(14) DPC_CASE(15) DPC_CASE(16)
+    }
+  }
+#undef DPC_CASE
   return launch_status();
 }
 
@@ -1844,7 +1883,11 @@ template <typename TI, typename TO, bool kFromD = false>
 int launch_bwd_mfma(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
                     const int* nlist, const void* em, const void* dT, void* dR,
                     const double* Tin = nullptr, const double* dD = nullptr) {
-  switch (split_of(g.nloc, 1280, 6144)) {
+  // above 128 channels (S > 8), us unsplit / kBySet / kByRun: float64 256: 94 / 45 / 20, 1,372:
+  // 109 / 62 / 56, 2,048: 109 / 64 / 74, 4,000: 109 / 117 / 133; mixed 5,184: 202 / 254 / 148, 12,288: 331 / 505 / 330
+  const bool wide = g.m1 > 16 * kMfmaWide;
+  switch (!wide ? split_of(g.nloc, 1280, 6144)
+                : (sizeof(TI) == 4 ? split_of(g.nloc, 8192, 8192) : split_of(g.nloc, 1536, 3072))) {
     case Split::kByRun: return launch_mfma_split<TI, TO, kFromD, 1, 8>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
     case Split::kBySet: return launch_mfma_split<TI, TO, kFromD, kMfmaAtoms, 4>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
     default: return launch_mfma_split<TI, TO, kFromD, kMfmaAtoms, 1>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
@@ -1878,13 +1921,14 @@ int launch_bwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
   // float64 and the mixed mode (float64 accumulation) on the matrix cores;
   // the float32 mode keeps float32 arithmetic on the vector ALUs
   if constexpr (sizeof(TA) == 8) {
-    if (g.m1 <= 128) return launch_bwd_mfma<TI, TA>(s, g, coeff, atype, nlist, em, dT, dR);
-  }
-  constexpr int NB = DPC_BWD_ATOMS_PER_WAVE;
-  switch (split_of(g.nloc, 640, 1536)) {
-    case Split::kByRun: return launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR);
-    case Split::kBySet: return launch_bwd_vec<TI, TA, NB, 4>(s, g, coeff, atype, nlist, em, dT, dR);
-    default: return launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
+    return launch_bwd_mfma<TI, TA>(s, g, coeff, atype, nlist, em, dT, dR);
+  } else {
+    constexpr int NB = DPC_BWD_ATOMS_PER_WAVE;
+    switch (split_of(g.nloc, 640, 1536)) {
+      case Split::kByRun: return launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR);
+      case Split::kBySet: return launch_bwd_vec<TI, TA, NB, 4>(s, g, coeff, atype, nlist, em, dT, dR);
+      default: return launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
+    }
   }
 }
 
@@ -1924,7 +1968,7 @@ extern "C" int dpc_se_a_tab_bwd_from_dD(void* stream, dpc_dtype dtype, int nloc,
   Geo g;
   const int st = make_geo(nloc, ntypes, sel, m1, m2, ranges, dtype == DPC_F64 ? 8 : 4, &g);
   if (st != DPC_OK) return st;
-  // float64, the matrix-core backward (M1 <= 128), M' even and at most 16
+  // float64, M1 <= 128 (the prologue's K steps), M' even and at most 16
   if (dtype != DPC_F64 || m1 > 128 || m2 > 16 || m2 % 2) return DPC_ENOTSUP;
   if (nloc == 0) return DPC_OK;
   if (!coeff || !atype || !nlist || !em || !T || !dE_dD || !dE_dem) return DPC_EINVAL;
