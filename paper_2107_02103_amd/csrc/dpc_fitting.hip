@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void tanh_grad_kernel(int64_t nw, int w, const
 // atoms leave most of the chip idle, and the products need ten passes over the
 // activations between them.  Energy and dE/dD, n_in 1,600, us through rocBLAS
 // and here: 256 atoms 149 / 52, 1,000: 121 / 111, 2,048: 157 / 158, 4,096:
-// 237 / 227, 12,288: 629 / 552, 131,072: 5,201 / 4,460, 1,048,576: 39,700 / 35,100.
+// 237 / 227, 12,288: 629 / 518, 131,072: 5,201 / 4,460, 1,048,576: 39,700 / 35,100.
 constexpr int kFw = 240, kFt = kFw / 16;   // width, and its tiles
 constexpr int kXcd = 8;                    // workgroups go to the XCDs in turn
 
@@ -712,6 +712,9 @@ int fit_240(hipStream_t s, int n, const dpc_fitting_net* net, const double* D, d
   };
   // at most one workgroup of 16 atoms per CU: a tile per wavefront (4,096 atoms: 62 us, 85 with 32 atoms)
   if (n <= 16 * kCus) middle(fit_middle_kernel<1, 16>, 1, 16);
+  // three atom tiles where they leave fewer of them per CU (12,288 atoms: 256
+  // workgroups, 131 us; 384 with two tiles, 163)
+  else if (3 * ceil_div(ceil_div(n, 48), kCus) < 2 * ceil_div(ceil_div(n, 32), kCus)) middle(fit_middle_kernel<3, 16>, 3, 16);
   else middle(fit_middle_kernel<2, 8>, 2, 8);
   if (dD) launch_input_grad(s, n, nin, dz1, net->W[0], dD);
   return dpc_internal_launch_status();

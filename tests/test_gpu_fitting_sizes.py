@@ -54,7 +54,7 @@ def _errors(net, D, E, G):
     return np.max(np.abs(E - Er)) / np.max(np.abs(Er)), np.max(np.abs(G - Gr).reshape(len(Gr), -1).max(1) / scale)
 
 
-@pytest.mark.parametrize("n", [1, 15, 17, 64, 65, 512, 513, 2048, 2049, 4096, 4097, 8300])
+@pytest.mark.parametrize("n", [1, 15, 17, 64, 65, 512, 513, 2048, 2049, 4096, 4097, 8200, 12289])
 def test_atom_counts(n):
     net = Net(100 * 4, 240, 3)
     D = np.random.default_rng(n).standard_normal((n, 100, 4))
