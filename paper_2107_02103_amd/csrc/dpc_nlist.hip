@@ -12,7 +12,8 @@
 // at a cell face cannot put two atoms closer than r_c two cells apart).
 //   1. zero the counters;  2. cell of each atom, counted with atomics;
 //   3. exclusive scan (one workgroup);  4. scatter the atoms into cell order
-//   with their coordinates, index and type packed in 32 bytes;
+//   with their coordinates, index and type packed in 32 bytes (1 to 4 in one
+//   workgroup for small systems);
 //   5. one wavefront per atom walks the (up to) 27 cells around its own as
 //   column spans of the cell-ordered array, 64 candidates at a time with
 //   the next batch in flight, keeps those within r_c in LDS, ranks each of
@@ -87,17 +88,99 @@ __device__ __forceinline__ int cell_axis(double x, const NlGeo& g) {
   return (int)fmin(fmax(w * g.inv_cs, 0.0), (double)(g.nc - 1));
 }
 
-__global__ void nl_zero_kernel(int n, int* __restrict__ p) {
+__device__ __forceinline__ int cell_index(const double* p, const NlGeo& g) {
+  return (cell_axis(p[0], g) * g.nc + cell_axis(p[1], g)) * g.nc + cell_axis(p[2], g);
+}
+
+// atom i at place p of the cell order
+__device__ __forceinline__ void put_atom(const NlGeo& g, const double* __restrict__ coord,
+                                         const int* __restrict__ atype, int i, int p,
+                                         NlAtom* __restrict__ sorted) {
+  const double* c = coord + 3 * (size_t)i;
+  NlAtom a;
+  a.x = c[0];
+  a.y = c[1];
+  a.z = c[2];
+  a.j = i | (in_box(c, g) ? 0 : kOutside);
+  a.type = atype[i];
+  if (a.type < 0 || a.type >= g.ntypes) a.x = (double)NAN;
+  sorted[p] = a;
+}
+
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ int wave_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
+}
+
+// the counters and the two status words
+__global__ void nl_zero_kernel(int n, int* __restrict__ p, int* __restrict__ status) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
+  if (i < 2) status[i] = 0;
+}
+
+// Small systems: counters, cells, scan and scatter in one workgroup, with the
+// counters in LDS.  Four launches of a few microseconds each become one, until
+// one workgroup's passes over the atoms cost more.  Whole build, us, four
+// launches and one: 256 atoms 24.9 / 14.4, 2,048: 36 / 20, 6,912: 73 / 55,
+// 8,232: 53 / 49, 12,288: 63 / 67, 16,384: 66 / 75.
+constexpr int kOneMaxCells = 4096, kOneMaxAtoms = 8192;
+__global__ __launch_bounds__(kScanThreads) void nl_cells_one_kernel(const NlGeo g, const double* __restrict__ coord,
+                                                                    const int* __restrict__ atype,
+                                                                    int* __restrict__ start,
+                                                                    int* __restrict__ cell_of,
+                                                                    NlAtom* __restrict__ sorted,
+                                                                    int* __restrict__ status) {
+  __shared__ int cursor[kOneMaxCells];
+  __shared__ int part[kScanThreads / 64];
+  const int t = threadIdx.x;
+  if (t < 2) status[t] = 0;
+  for (int c = t; c < g.ncell; c += kScanThreads) cursor[c] = 0;
+  __syncthreads();
+  for (int i = t; i < g.nloc; i += kScanThreads) {
+    const int c = cell_index(coord + 3 * (size_t)i, g);
+    cell_of[i] = c;
+    atomicAdd(cursor + c, 1);
+  }
+  __syncthreads();
+  // exclusive scan: kPer consecutive cells per thread, wavefronts' sums through LDS
+  constexpr int kPer = kOneMaxCells / kScanThreads;
+  int v[kPer], sum = 0;
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    v[k] = kPer * t + k < g.ncell ? cursor[kPer * t + k] : 0;
+    sum += v[k];
+  }
+  const int upto = wave_scan(sum);
+  if ((t & 63) == 63) part[t >> 6] = upto;
+  __syncthreads();
+  int run = upto - sum;
+  for (int w = 0; w < (t >> 6); ++w) run += part[w];
+#pragma unroll
+  for (int k = 0; k < kPer; ++k) {
+    if (kPer * t + k < g.ncell) {
+      start[kPer * t + k] = run;
+      cursor[kPer * t + k] = run;
+    }
+    run += v[k];
+  }
+  if (t == 0) start[g.ncell] = g.nloc;
+  __syncthreads();
+  for (int i = t; i < g.nloc; i += kScanThreads)
+    put_atom(g, coord, atype, i, atomicAdd(cursor + cell_of[i], 1), sorted);
 }
 
 __global__ void nl_cell_kernel(const NlGeo g, const double* __restrict__ coord,
                                int* __restrict__ count, int* __restrict__ cell_of) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= g.nloc) return;
-  const double* p = coord + 3 * (size_t)i;
-  const int c = (cell_axis(p[0], g) * g.nc + cell_axis(p[1], g)) * g.nc + cell_axis(p[2], g);
+  const int c = cell_index(coord + 3 * (size_t)i, g);
   cell_of[i] = c;
   atomicAdd(count + c, 1);
 }
@@ -136,16 +219,7 @@ __global__ void nl_scatter_kernel(const NlGeo g, const double* __restrict__ coor
                                   NlAtom* __restrict__ sorted) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= g.nloc) return;
-  const int p = atomicAdd(cursor + cell_of[i], 1);
-  const double* c = coord + 3 * (size_t)i;
-  NlAtom a;
-  a.x = c[0];
-  a.y = c[1];
-  a.z = c[2];
-  a.j = i | (in_box(c, g) ? 0 : kOutside);
-  a.type = atype[i];
-  if (a.type < 0 || a.type >= g.ntypes) a.x = (double)NAN;
-  sorted[p] = a;
+  put_atom(g, coord, atype, i, atomicAdd(cursor + cell_of[i], 1), sorted);
 }
 
 __device__ __forceinline__ uint64_t ballot(bool b) { return __ballot(b); }
@@ -172,17 +246,6 @@ __device__ __forceinline__ unsigned count_before(uint64_t or2, uint32_t ojt, uin
 
 __device__ __forceinline__ int lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0));
-}
-
-// Inclusive sum over the lanes of a wavefront.
-__device__ __forceinline__ int wave_scan(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);   // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return v;
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -575,13 +638,17 @@ static int dpc_nlist_launch(void* stream, int nloc, int ntypes, const int* sel, 
   NlAtom* sorted = reinterpret_cast<NlAtom*>(w + L.sorted);
   hipStream_t s = static_cast<hipStream_t>(stream);
   (void)hipGetLastError();  // report only what these launches raise
-  // the counters and the status words start at zero (a fill kernel, not a memset)
-  hipLaunchKernelGGL(nl_zero_kernel, dim3(1), dim3(64), 0, s, 2, status);
-  hipLaunchKernelGGL(nl_zero_kernel, dim3((g.ncell + 255) / 256), dim3(256), 0, s, g.ncell, count);
   const dim3 ga((nloc + 255) / 256), b256(256);
-  hipLaunchKernelGGL(nl_cell_kernel, ga, b256, 0, s, g, coord, count, cell_of);
-  hipLaunchKernelGGL(nl_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, g.ncell, count, start, cursor);
-  hipLaunchKernelGGL(nl_scatter_kernel, ga, b256, 0, s, g, coord, atype, cell_of, cursor, sorted);
+  if (nloc <= kOneMaxAtoms && g.ncell <= kOneMaxCells) {
+    hipLaunchKernelGGL(nl_cells_one_kernel, dim3(1), dim3(kScanThreads), 0, s, g, coord, atype, start, cell_of,
+                       sorted, status);
+  } else {
+    // the counters and the status words start at zero (a fill kernel, not a memset)
+    hipLaunchKernelGGL(nl_zero_kernel, dim3((g.ncell + 255) / 256), b256, 0, s, g.ncell, count, status);
+    hipLaunchKernelGGL(nl_cell_kernel, ga, b256, 0, s, g, coord, count, cell_of);
+    hipLaunchKernelGGL(nl_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, g.ncell, count, start, cursor);
+    hipLaunchKernelGGL(nl_scatter_kernel, ga, b256, 0, s, g, coord, atype, cell_of, cursor, sorted);
+  }
   hipLaunchKernelGGL(ntypes == 1 ? nl_list_kernel<true> : nl_list_kernel<false>,
                      dim3((nloc + kNlWaves - 1) / kNlWaves), dim3(64 * kNlWaves), 0, s, g, coord, cell_of, start,
                      sorted, nlist, status);

@@ -92,6 +92,22 @@ def test_many_neighbours(near):
     _check(x, rng.integers(0, 2, size=len(x)), (400, 500), 40.0, 9.0)
 
 
+@pytest.mark.parametrize("n,box", [(1, 7.0), (8191, 30.0), (8192, 90.0), (8193, 30.0), (700, 200.0)])
+def test_cell_lists_of_one_workgroup_and_of_several(n, box):
+    # both sides of the largest system whose cells one workgroup sorts, few and
+    # many cells (4,096 are the most it takes; one cell per atom and axis at
+    # most), crowded and empty ones
+    rng = np.random.default_rng(n)
+    x = rng.uniform(0, box, size=(n, 3))
+    x[: n // 4] = rng.uniform(0, 2.0, size=(n // 4, 3)) + x[0]
+    a = np.ascontiguousarray(rng.integers(0, 2, size=n), np.int32)
+    c, at, nl, st = _build(x, a, (120, 120), box, 3.0)
+    pick = np.unique(rng.integers(0, n, 400))
+    ref, cnt, over = onl.neighbour_list(x, a, (120, 120), box, 3.0, centres=pick)
+    few = np.asarray(cnt).sum(1) <= 1024 if np.ndim(cnt) == 2 else np.ones(len(pick), bool)
+    np.testing.assert_array_equal(nl.cpu().numpy()[pick][few], ref[few])
+
+
 @pytest.mark.parametrize("sel", [(3,), (16,), (17, 2), (9, 40), (2, 20, 30)])
 def test_reverse_of_short_and_truncated_blocks(sel):
     rng = np.random.default_rng(sum(sel))
