@@ -361,6 +361,48 @@ __device__ __forceinline__ uint32_t occupied_chunks(uint32_t vm) {
   return occ;
 }
 
+// The share of one atom's records that one of kSplit wavefronts takes, by their
+// place among all of the atom's records in merged order (one window) or among
+// the chunk set's (longer lists).  A run goes to the wavefront whose share
+// holds its first record, and a chunk set's padding to the one that holds the
+// set's first record; a wavefront builds only the sets its share reaches
+// (building every set and taking a part of its runs took 16 us on 256 atoms
+// with 77 neighbours and 58 us on 1,372 with 180, this 16 and 45).
+template <int kSplit>
+struct RecordShare {
+  int lo = 0, hi = 0;          // this wavefront's records
+  int next = 0;                // records before the next chunk set
+  int base = 0, count = 0;     // of the current chunk set
+  bool whole = false;
+
+  // the list fits one window, whose validity bits are vm
+  __device__ __forceinline__ void all(uint32_t vm, int nch, int wave) {
+    int n = 0;
+    for (int c = 0; c < nch; ++c) n += __popcll(__ballot((vm >> c) & 1));
+    whole = true;
+    lo = wave * n / kSplit;
+    hi = (wave + 1) * n / kSplit;
+  }
+  // enter chunk set c of the window; false if no record of it is taken
+  __device__ __forceinline__ bool enter(uint32_t vm, int c, int wave) {
+    count = __popcll(__ballot((vm >> c) & 1));
+    if (whole) {
+      base = next;
+      next += count;
+    } else {
+      lo = wave * count / kSplit;
+      hi = (wave + 1) * count / kSplit;
+    }
+    return base + count > lo && base < hi;
+  }
+  __device__ __forceinline__ bool owner() const { return lo <= base && base < hi; }
+  // runs [r0, r1) of the set
+  __device__ __forceinline__ void runs(const Tables& tb, int lane, int& r0, int& r1) const {
+    r0 = __popcll(__ballot(lane < tb.nruns && base + tb.vs < lo));
+    r1 = __popcll(__ballot(lane < tb.nruns && base + tb.vs < hi));
+  }
+};
+
 // One R~ row (16-byte aligned: checked on the host).
 template <typename TI>
 __device__ __forceinline__ void load_row(const TI* p, TI (&r)[4]) {
@@ -768,6 +810,15 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
   int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
   int turn = 0, wbase = -1;
+  RecordShare<kSplit> share;
+  if constexpr (kShared && NB == 1) {
+    if (nnei <= kWindow) {
+      wbase = 0;
+      vm = valid_window<NB>(g, wa, 0, nlist, lane);
+      occ = occupied_chunks<NB>(vm);
+      share.all(vm, nch, wave);
+    }
+  }
   uint32_t taken = 0;          // chunk sets whose first-interval records the moments have taken
   if constexpr (NB == 4 && !kShared) {
     if (wa.idx[0] >= 0 && nnei <= kWindow / NB) {
@@ -786,14 +837,14 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
     }
     if (!((occ >> ((s0 - wbase) / kC)) & 1)) continue;   // padding only
     if (kShared && NB > 1 && turn++ % kSplit != wave) continue;
+    if (kShared && NB == 1 && !share.enter(vm, (s0 - wbase) / kC, wave)) continue;
     const Tables tb = build_chunk_set<TI, TA, NB, false, kOne>(g, ai, my_atom, s0, wbase, vm, em, W.z, W.s, lane,
                                                               nullptr, nullptr, false, nullptr,
                                                               (taken >> ((s0 - wbase) / kC)) & 1);
     if (tb.n == 0) continue;
     int r = 0, r1 = tb.nruns;
     if constexpr (kShared && NB == 1) {
-      r = wave * tb.nruns / kSplit;
-      r1 = (wave + 1) * tb.nruns / kSplit;
+      share.runs(tb, lane, r, r1);
       if (r == r1) continue;
     }
     load_coef<TI, CPL>(rs, key_offset(readlane(tb.vk, r)), ld, voff, cfA);
@@ -1041,8 +1092,17 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
   const int nch = (nnei + kC - 1) / kC;
   int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
-  int turn = 0;
-  for (int cc = 0, wbase = -1; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
+  int turn = 0, wbase = -1;
+  RecordShare<kSplit> share;
+  if constexpr (kShared && NB == 1) {
+    if (nnei <= kWindow) {
+      wbase = 0;
+      vm = valid_window<NB>(g, wa, 0, nlist, lane);
+      occ = occupied_chunks<NB>(vm);
+      share.all(vm, nch, wave);
+    }
+  }
+  for (int cc = 0; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
     if (s0 - s0 % (kWindow / NB) != wbase) {  // window of nlist signs holding s0
       wbase = s0 - s0 % (kWindow / NB);
       vm = valid_window<NB>(g, wa, wbase, nlist, lane);
@@ -1053,21 +1113,21 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
       continue;
     }
     if (kShared && NB > 1 && turn++ % kSplit != wave) continue;
+    if (kShared && NB == 1 && !share.enter(vm, (s0 - wbase) / kC, wave)) continue;
     const Tables tb = build_chunk_set<TI, TA, NB, true, kOne>(g, ai, my_atom, s0, wbase, vm, em, W.z, W.s, lane);
     // Each lane writes the dE/dR~ row of its own slot (zero for padding) after
     // the chunk set's runs: consecutive lanes, consecutive rows, and no store
     // ahead of the coefficient loads whose waits would then include it.
     // Of a chunk set whose runs are shared out, a wavefront writes the records
-    // of its runs, [e_lo, e_hi) in merged order; the first one also the padding.
+    // of its runs, [e_lo, e_hi) in merged order; one of them also the padding.
     int r = 0, r1 = tb.nruns, e_lo = 0, e_hi = tb.n;
     if constexpr (kShared && NB == 1) {
-      r = wave * tb.nruns / kSplit;
-      r1 = (wave + 1) * tb.nruns / kSplit;
+      share.runs(tb, lane, r, r1);
       e_lo = readlane(tb.vs, r < kLanes ? r : kLanes - 1);
       e_hi = r1 < kLanes ? readlane(tb.vs, r1) : tb.n;
     }
     auto write_rows = [&]() __attribute__((always_inline)) {
-      if (kShared && NB == 1 && (tb.rank < 0 ? wave > 0 : tb.rank < e_lo || tb.rank >= e_hi)) return;
+      if (kShared && NB == 1 && (tb.rank < 0 ? !share.owner() : tb.rank < e_lo || tb.rank >= e_hi)) return;
       if (tb.rank >= -1) {
         TA v[4] = {(TA)0, (TA)0, (TA)0, (TA)0};
         if (tb.rank >= 0) {
@@ -1548,10 +1608,19 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
   const int nch = (nnei + kC - 1) / kC;
   int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
-  int turn = 0;
+  int turn = 0, wbase = -1;
+  RecordShare<kSplit> share;
+  if constexpr (kShared && NB == 1) {
+    if (nnei <= kWindow) {
+      wbase = 0;
+      vm = valid_window<NB>(g, wa, 0, nlist, lane);
+      occ = occupied_chunks<NB>(vm);
+      share.all(vm, nch, wave);
+    }
+  }
   TI pre[4];          // R~ rows of chunk set pre_s0, loaded ahead (valid slots use them)
   int pre_s0 = -1;
-  for (int cc = 0, wbase = -1; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
+  for (int cc = 0; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
     if (s0 - s0 % (kWindow / NB) != wbase) {  // window of nlist signs holding s0
       wbase = s0 - s0 % (kWindow / NB);
       vm = valid_window<NB>(g, wa, wbase, nlist, lane);
@@ -1562,6 +1631,7 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
       continue;
     }
     if (kShared && NB > 1 && turn++ % kSplit != wave) continue;
+    if (kShared && NB == 1 && !share.enter(vm, (s0 - wbase) / kC, wave)) continue;
     int pair;
     Rec<TI> mine;
     const Tables tb = build_chunk_set<TI, double, NB, true, kOne, true>(
@@ -1569,12 +1639,12 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
     // the rows of the next chunk set are loaded during this one's last run
     const int s0n = s0 + kC < nnei ? s0 + kC : 0;
     // (not when the window already shows that set to hold padding only)
-    const bool more = !(kShared && NB > 1) && cc + 1 < nch &&
+    const bool more = !kShared && cc + 1 < nch &&
                       (s0n - s0n % (kWindow / NB) != wbase || ((occ >> ((s0n - wbase) / kC)) & 1));
     double out[4] = {0.0, 0.0, 0.0, 0.0};   // this lane's dE/dR~ row
     // this wavefront's runs: all, or its share (NB = 1: a run is one product)
-    const int r0 = kShared && NB == 1 ? wave * tb.nruns / kSplit : 0;
-    const int r1 = kShared && NB == 1 ? (wave + 1) * tb.nruns / kSplit : tb.nruns;
+    int r0 = 0, r1 = tb.nruns;
+    if constexpr (kShared && NB == 1) share.runs(tb, lane, r0, r1);
     if (kShared ? r0 < r1 : tb.n > 0) {
       // the lanes whose records belong to pairs [base, base + np) read their products
       auto eval = [&](int base, int np) __attribute__((always_inline)) {
@@ -1690,7 +1760,7 @@ void se_a_bwd_mfma_kernel(const Geo g, const TI* __restrict__ coeff,
       run(r1 - 1, std::true_type{});
     }
     // each lane writes the dE/dR~ row of its own slot (zero for padding)
-    const bool mine_out = !(kShared && NB == 1) || (tb.rank < 0 ? wave == 0 : pair >= r0 && pair < r1);
+    const bool mine_out = !(kShared && NB == 1) || (tb.rank < 0 ? share.owner() : pair >= r0 && pair < r1);
     if (tb.rank >= -1 && mine_out) {
       const TO o[4] = {(TO)out[0], (TO)out[1], (TO)out[2], (TO)out[3]};
       store_row(dR + ((size_t)my_atom * nnei + s0 + lane % kC) * 4, o);
@@ -1766,10 +1836,12 @@ int make_geo(int nloc, int ntypes, const int* sel, int m1, int m2, const dpc_ran
 // runs of one atom.  Both fetch more coefficients per atom.  `run_max` and
 // `set_max` are the atom counts up to which they win (us per call, unsplit /
 // kBySet / kByRun, M1 = 100, float64 unless noted):
-//   forward    256: 67 / 33 / 16    1,372: 70 / 38 / 37    4,000: 76 / 73 / 87    6,912: 90 / 109 / 146
-//   matrix bwd 256: 69 / 32 / 16    1,372: 72 / 39 / 35    4,000: 77 / 76 / 85    6,912: 104 / 112 / 142
-//   vector bwd (float32) 256: 48 / 25 / 16    864: 50 / 29 / 30    1,372: 51 / 33 / 34    2,048: 52 / 52 / 47
-//   forward, M1 = 200    500: 69 / 47 / 36    864: 75 / 48 / 67    1,372: 83 / 92 / 101
+//   forward    256: 67 / 33 / 16    1,372: 70 / 38 / 32    2,048: 70 / 40 / 42    4,000: 76 / 73 / 89    6,912: 90 / 109 / 146
+//   float32    2,048: - / 34 / 28    4,000: - / 42 / 50
+//   matrix bwd 256: 69 / 32 / 16    1,372: 72 / 39 / 34    2,048: - / 42 / 45    4,000: 77 / 76 / 85    6,912: 104 / 112 / 142
+//   vector bwd (float32) 256: 48 / 25 / 16    864: 50 / 29 / 22    2,048: 52 / 52 / 35    4,000: 61 / 86 / 63;
+//     lists of 40 neighbours 3,000: 70 / 63 / 56    5,184: 83 / 106 / 92
+//   forward, M1 = 200    500: 69 / 47 / 36    864: 75 / 47 / 58    1,372: 83 / 92 / 101
 // (lists of 77 neighbours; with 180, kBySet wins up to about 10,000 atoms).
 enum class Split { kNone, kBySet, kByRun };
 Split split_of(int nloc, int run_max, int set_max) {
@@ -1813,7 +1885,8 @@ template <typename TI, typename TA>
 int launch_fwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
                const void* em, void* T, void* D) {
   // more than 128 channels: fewer wavefronts fit at once with four channels per lane
-  switch (g.m1 <= 128 ? split_of(g.nloc, 1280, 6144) : split_of(g.nloc, 512, sizeof(TI) == 8 ? 1024 : 2048)) {
+  switch (g.m1 <= 128 ? split_of(g.nloc, sizeof(TI) == 8 ? 1536 : 2048, 6144)
+                       : split_of(g.nloc, 512, sizeof(TI) == 8 ? 1024 : 2048)) {
     case Split::kByRun: return launch_fwd_split<TI, TA, 1, 8>(s, g, coeff, atype, nlist, em, T, D);
     case Split::kBySet: return launch_fwd_split<TI, TA, DPC_FWD_ATOMS_PER_WAVE, 4>(s, g, coeff, atype, nlist, em, T, D);
     default:
@@ -1869,6 +1942,7 @@ int launch_mfma_split(hipStream_t s, const Geo& g, const void* coeff, const int*
     break;
   switch (S) {
     DPC_CASE(1) DPC_CASE(2) DPC_CASE(3) DPC_CASE(4) DPC_CASE(5) DPC_CASE(6) DPC_CASE(7) DPC_CASE(8)
+
   }
   if constexpr (!kFromD) {
     switch (S) {
@@ -1924,7 +1998,7 @@ int launch_bwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
     return launch_bwd_mfma<TI, TA>(s, g, coeff, atype, nlist, em, dT, dR);
   } else {
     constexpr int NB = DPC_BWD_ATOMS_PER_WAVE;
-    switch (split_of(g.nloc, 640, 1536)) {
+    switch (g.m1 <= 128 ? split_of(g.nloc, 3072, 3072) : split_of(g.nloc, 640, 1536)) {
       case Split::kByRun: return launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR);
       case Split::kBySet: return launch_bwd_vec<TI, TA, NB, 4>(s, g, coeff, atype, nlist, em, dT, dR);
       default: return launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
