@@ -820,7 +820,9 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
     }
   }
   uint32_t taken = 0;          // chunk sets whose first-interval records the moments have taken
-  if constexpr (NB == 4 && !kShared) {
+  // (float32 with four channels per lane fits twice as many wavefronts without them:
+  // M1 = 200, 10,125 atoms with 40 neighbours 226 us with, 163 without)
+  if constexpr (NB == 4 && !kShared && !(CPL == 4 && sizeof(TA) == 4)) {
     if (wa.idx[0] >= 0 && nnei <= kWindow / NB) {
       wbase = 0;
       vm = valid_window<NB>(g, wa, 0, nlist, lane);
@@ -1958,10 +1960,10 @@ int launch_bwd_mfma(hipStream_t s, const Geo& g, const void* coeff, const int* a
                     const int* nlist, const void* em, const void* dT, void* dR,
                     const double* Tin = nullptr, const double* dD = nullptr) {
   // above 128 channels (S > 8), us unsplit / kBySet / kByRun: float64 256: 94 / 45 / 20, 1,372:
-  // 109 / 62 / 56, 2,048: 109 / 64 / 74, 4,000: 109 / 117 / 133; mixed 5,184: 202 / 254 / 148, 12,288: 331 / 505 / 330
+  // 109 / 62 / 56, 2,048: 109 / 64 / 74, 4,000: 109 / 117 / 133; mixed 5,184: 197 / - / 152, 8,788: 430 / - / 323, 16,384: 532 / - / 585
   const bool wide = g.m1 > 16 * kMfmaWide;
   switch (!wide ? split_of(g.nloc, 1280, 6144)
-                : (sizeof(TI) == 4 ? split_of(g.nloc, 8192, 8192) : split_of(g.nloc, 1536, 3072))) {
+                : (sizeof(TI) == 4 ? split_of(g.nloc, 10240, 10240) : split_of(g.nloc, 1536, 3072))) {
     case Split::kByRun: return launch_mfma_split<TI, TO, kFromD, 1, 8>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
     case Split::kBySet: return launch_mfma_split<TI, TO, kFromD, kMfmaAtoms, 4>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
     default: return launch_mfma_split<TI, TO, kFromD, kMfmaAtoms, 1>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
@@ -1981,23 +1983,46 @@ int launch_bwd_vec(hipStream_t s, const Geo& g, const void* coeff, const int* at
     hipLaunchKernelGGL(kern, grid, block, shm, s, g, (const TI*)coeff, atype, nlist,
                        (const TI*)em, (const TI*)dT, (TA*)dR);
   };
-  switch (channels_per_lane(g.m1)) {
-    case 1: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 1, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 1, NB, false, kSplit>); break;
-    case 2: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 2, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 2, NB, false, kSplit>); break;
-    default: g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 4, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 4, NB, false, kSplit>); break;
+  const int cpl = channels_per_lane(g.m1);
+  if constexpr (sizeof(TA) == 4) {
+    if (cpl == 1) {
+      g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 1, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 1, NB, false, kSplit>);
+      return launch_status();
+    }
+    if (cpl == 2) {
+      g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 2, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 2, NB, false, kSplit>);
+      return launch_status();
+    }
   }
+  // (float64 accumulation: only above 128 channels)
+  g.ntypes == 1 ? go(se_a_bwd_kernel<TI, TA, 4, NB, true, kSplit>) : go(se_a_bwd_kernel<TI, TA, 4, NB, false, kSplit>);
   return launch_status();
 }
+
+// The mixed mode with many channels: the matrix-core kernel pays for whole
+// 16-channel steps and for two wavefronts per SIMD, which short lists (few
+// records per run) and the widest nets do not return.  us, matrix cores /
+// vector ALUs, unsplit: M1 = 129, 10,125 atoms of 138 slots 259 / 271; M1 = 200,
+// 12,288 of 138 328 / 311, 16,384 of 420 532 / 601; M1 = 256, 24,000 of 138
+// 668 / 608, 32,000 of 420 1,201 / 1,186.
+inline bool mixed_on_vector_alus(const Geo& g) { return g.m1 > 208 || (g.m1 > 160 && g.nnei <= 256); }
 
 template <typename TI, typename TA>
 int launch_bwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
                const void* em, const void* dT, void* dR) {
-  // float64 and the mixed mode (float64 accumulation) on the matrix cores;
-  // the float32 mode keeps float32 arithmetic on the vector ALUs
+  constexpr int NB = DPC_BWD_ATOMS_PER_WAVE;
   if constexpr (sizeof(TA) == 8) {
+    if constexpr (sizeof(TI) == 4) {
+      if (mixed_on_vector_alus(g)) {
+        // (us unsplit / kByRun, M1 = 256, 138 slots: 1,536: 86 / 55, 6,591: 211 / 195, 10,125: 294 / 313)
+        return g.nloc <= 8192 ? launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR)
+                               : launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
+      }
+    }
+    // the rest of float64 and the mixed mode (float64 accumulation) on the matrix cores
     return launch_bwd_mfma<TI, TA>(s, g, coeff, atype, nlist, em, dT, dR);
   } else {
-    constexpr int NB = DPC_BWD_ATOMS_PER_WAVE;
+    // the float32 mode keeps float32 arithmetic on the vector ALUs
     switch (g.m1 <= 128 ? split_of(g.nloc, 3072, 3072) : split_of(g.nloc, 640, 1536)) {
       case Split::kByRun: return launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR);
       case Split::kBySet: return launch_bwd_vec<TI, TA, NB, 4>(s, g, coeff, atype, nlist, em, dT, dR);

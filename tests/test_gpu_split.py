@@ -21,7 +21,9 @@ BAD, EMPTY = 7, 11
                                              ((3, 70), 100, 16, "f32"), ((64,), 100, 16, "f32acc64"),
                                              ((40, 33), 200, 16, "f32acc64"),
                                              ((40, 33), 200, 16, "f64"), ((70,), 256, 16, "f64"),
-                                             ((20, 30), 137, 8, "f32acc64"), ((40,), 241, 5, "f32")])
+                                             ((20, 30), 137, 8, "f32acc64"), ((40,), 241, 5, "f32"),
+                                             ((20, 31), 161, 8, "f32acc64"), ((30, 241), 208, 8, "f32acc64"),
+                                             ((30, 241), 209, 8, "f32acc64"), ((70,), 256, 16, "f32acc64")])
 def test_every_mapping_matches_the_oracle(sel, m1, m2, dtype):
     import paper_2107_02103_amd as P
     x = edge_inputs(BASE, sel, m1, m2, seed=sum(sel) + m1 + 29)
@@ -37,7 +39,7 @@ def test_every_mapping_matches_the_oracle(sel, m1, m2, dtype):
     for k in (0, 3):
         base[k] = base[k].to(op.t_in)
     for n in (1, 512, 513, 640, 641, 1024, 1025, 1280, 1281, 1536, 1537, 2048, 2049, 3072, 3073, 6144, 6145, 6161,
-              8192, 8193):
+              8192, 8193, 10240, 10241):
         em, nl, at, dT = (t.repeat((n // BASE + 1,) + (1,) * (t.dim() - 1))[:n].contiguous() for t in base)
         out = (*op.forward(em, nl, at), op.backward(em, nl, at, dT))
         out = [t.cpu().numpy().astype(np.float64) for t in out]
