@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "dpc.h"
+#include "dpc_fit_tiles.h"
 #include "dpc_internal.h"
 
 namespace {
@@ -165,7 +166,6 @@ __global__ __launch_bounds__(256) void tanh_grad_kernel(int64_t nw, int w, const
 // activations between them.  Energy and dE/dD, n_in 1,600, us through rocBLAS
 // and here: 256 atoms 149 / 52, 1,000: 121 / 111, 2,048: 157 / 158, 4,096:
 // 237 / 227, 12,288: 629 / 518, 131,072: 5,201 / 4,460, 1,048,576: 39,700 / 35,100.
-constexpr int kFw = 240, kFt = kFw / 16;   // width, and its tiles
 constexpr int kXcd = 8;                    // workgroups go to the XCDs in turn
 
 typedef double D2 __attribute__((ext_vector_type(2)));
@@ -428,12 +428,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int a0 = (int)blockIdx.x * 16 * MT;
   const int i = lane & 15, kk = lane >> 4, ch = 4 * (i & 3) + (i >> 2);
+  static_assert(fit_tiles_ok(NW), "every tile a wavefront reads exists");
   int tile[kTp];
   bool own[kTp];
 #pragma unroll
   for (int u = 0; u < kTp; ++u) {
-    own[u] = wave + NW * u < kFt;
-    tile[u] = own[u] ? wave + NW * u : wave;     // a tile of its own again: nothing is kept
+    own[u] = fit_owns(wave, NW, u);
+    tile[u] = fit_tile(wave, NW, u);
   }
   D4 T2[kTp][MT], G[kTp][MT], acc[kTp][MT];
   // t1 of the wavefront's tiles (read again at the end, not held meanwhile)
