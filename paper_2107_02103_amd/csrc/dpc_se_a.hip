@@ -705,11 +705,12 @@ __device__ __forceinline__ uint32_t first_interval_moments(
     sq[blk4 * 24 + kk * 4 + x] = q03;
     if (kk < 2) sq[blk4 * 24 + 16 + kk * 4 + x] = q45;
     wave_sync();
+    // one type: one table, whichever of the atoms are valid
+    if constexpr (kOne) load_coef<TI, CPL>(rs, g.pr[0].offset, ld, voff, cf);
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       if (ai[b] < 0) continue;
-      if (!kOne || b == 0)
-        load_coef<TI, CPL>(rs, g.pr[kOne ? 0 : ai[b] * g.ntypes + beta].offset, ld, voff, cf);
+      if constexpr (!kOne) load_coef<TI, CPL>(rs, g.pr[ai[b] * g.ntypes + beta].offset, ld, voff, cf);
       if (!active) continue;
 #pragma unroll
       for (int q = 0; q < 6; ++q) {

@@ -2,7 +2,8 @@
 atoms, or 1,024 above 128 channels; type blocks of 128 slots and more) against
 the oracle: lists whose tail, or a random part, lies in the first interval or
 below the table, whole chunk sets of such records, blocks too short to be
-looked at, non-finite rows, an invalid type, lists of more than one window."""
+looked at, non-finite rows, an invalid atom at every place of a wavefront, lists
+of more than one window."""
 import numpy as np
 import pytest
 
@@ -72,3 +73,53 @@ def test_matches_the_oracle(sel, m1, m2, dtype, n, order):
     assert all(np.isnan(g[rows == BAD]).all() for g in out)
     for g, r in zip(out, nan_ref):                       # NaN where the oracle has it
         np.testing.assert_array_equal(np.isfinite(g[rows == NAN]), np.isfinite(np.repeat(r, (rows == NAN).sum(), 0)))
+
+
+QUADS = 20         # rows of five wavefronts: an invalid atom at each of the four places, and none
+
+
+def _quadruples(sel, m1, m2, seed):
+    """Sorted full lists whose last chunk sets hold first-interval records only, so that every wavefront takes
+    moments; row 5 p (place p of wavefront p) is to become invalid, p = 0..3."""
+    x = edge_inputs(QUADS, sel, m1, m2, seed=seed)
+    rng = np.random.default_rng(seed)
+    lo, d1, nnei = x.lo[0], x.cfg.d1, sel[0]
+    near = rng.integers(40, 60, size=QUADS)
+    x.nlist[:] = 0
+    for i in range(QUADS):
+        v = np.concatenate([np.sort(rng.uniform(1.0, 280.0, nnei - near[i]))[::-1], rng.uniform(-0.3, 1.0, near[i])])
+        x.em[i, :, 0] = lo + d1 * v
+        x.em[i, :, 1:] = rng.normal(size=(nnei, 3))
+    bad = np.array([5 * p for p in range(4)])
+    x.nlist[bad, nnei // 2:] = -1                        # it decides nothing about the chunk sets looked at
+    x.em[x.nlist < 0] = 0
+    # every wavefront's last chunk set (16 slots an atom) holds at least 12 first-interval records of valid atoms
+    last = (nnei - 1) // 16 * 16
+    first = (x.nlist >= 0) & (x.em[..., 0] < lo + d1)
+    first[bad] = False
+    assert (first[:, last:].reshape(QUADS // 4, -1).sum(1) >= 12).all()
+    return x, bad
+
+
+@pytest.mark.parametrize("sel,m1,m2,dtype,n", [((200,), 100, 16, "f64", 6160), ((200,), 60, 8, "f64", 6150),
+                                               ((200,), 200, 16, "f64", 1040), ((160,), 100, 16, "f32", 6160),
+                                               ((500,), 128, 16, "f32acc64", 6160),
+                                               ((200,), 200, 16, "f32acc64", 2080)])
+def test_invalid_atom_at_every_place_of_a_wavefront(sel, m1, m2, dtype, n):
+    import paper_2107_02103_amd as P
+    x, bad = _quadruples(sel, m1, m2, m1 + sel[0])
+    good = np.setdiff1d(np.arange(QUADS), bad)
+    ref = oracle_fwd_bwd(x, good, dtype)[:2]
+    x.atype[bad] = (-1, 1, -7, 100)
+    c = x.cfg
+    mode = {"f64": P.DPC_F64, "f32": P.DPC_F32, "f32acc64": P.DPC_F32_ACC64}[dtype]
+    op = P.SeATab(x.nets, x.lo, x.L1, x.L2, c.d1, c.d2, c.sel, c.m2, dtype=mode)
+    em, nl, at = (torch.from_numpy(v).cuda().repeat((n // QUADS + 1,) + (1,) * (v.ndim - 1))[:n].contiguous()
+                  for v in (x.em, x.nlist, x.atype))
+    out = [t.cpu().numpy().astype(np.float64) for t in op.forward(em.to(op.t_in), nl, at)]
+    rows = np.arange(n) % QUADS
+    ok = np.isin(rows, good)
+    err = [normwise(g[ok], r[np.searchsorted(good, rows[ok])]) for g, r in zip(out, ref)]
+    print(f"[gpu-first] invalid atoms, sel {sel} m1 {m1} {dtype}: {err}", flush=True)
+    assert max(err) <= TOL[dtype], err
+    assert all(np.isnan(g[~ok]).all() for g in out)
