@@ -147,9 +147,15 @@ __device__ __forceinline__ void locate(const PairRange& P, double x, int& l, dou
   }
 }
 
-// A record that the forward's moments of the first interval may take (t^5
-// stays far from overflow).
-__device__ __forceinline__ bool first_interval(int l, double t) { return l == 0 && fabs(t) < 1e8; }
+// A record that the forward's moments of the first interval may take: t^5 r
+// stays far from overflow.  An infinite or NaN component does not pass: times
+// the polynomial it stays infinite, but t^q times it, summed over coefficients
+// of either sign, would not.
+template <typename TI>
+__device__ __forceinline__ bool first_interval(int l, double t, const TI (&r)[4]) {
+  const TI big = sizeof(TI) == 8 ? (TI)1e200 : (TI)1e38;
+  return l == 0 && fabs(t) < 1e8 && fabs(r[1]) < big && fabs(r[2]) < big && fabs(r[3]) < big;
+}
 
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -502,7 +508,7 @@ __device__ __forceinline__ Tables build_chunk_set(const Geo& g, const int (&ai)[
       locate(P, (double)rec.r[0], l, rec.t, cl);
       rec.pad = 0.0;
       key = (blk << kOffBits) | (kOffMask - (P.offset + l * 6 * g.ld));
-      if (drop_first && first_interval(l, rec.t)) valid = false;
+      if (drop_first && first_interval<TI>(l, rec.t, rec.r)) valid = false;
       // beyond the table the derivative term vanishes: a zero row removes it
       // (a NaN or infinite x keeps its row, so that it propagates)
       if (kBwd && cl && isfinite(rec.r[0])) {
@@ -678,7 +684,7 @@ __device__ __forceinline__ uint32_t first_interval_moments(
         int l;
         bool cl;
         locate(P, (double)r[0], l, t, cl);
-        hit = first_interval(l, t);
+        hit = first_interval<TI>(l, t, r);
       }
       const uint64_t mh = __ballot(hit);
       if (__popcll(mh) < kTakeMin) break;

@@ -2,7 +2,7 @@
 atoms, or 1,024 above 128 channels; type blocks of 128 slots and more) against
 the oracle: lists whose tail, or a random part, lies in the first interval or
 below the table, whole chunk sets of such records, blocks too short to be
-looked at, non-finite rows, an invalid atom at every place of a wavefront, lists
+looked at, NaN and infinite rows, an invalid atom at every place of a wavefront, lists
 of more than one window."""
 import numpy as np
 import pytest
@@ -123,3 +123,29 @@ def test_invalid_atom_at_every_place_of_a_wavefront(sel, m1, m2, dtype, n):
     print(f"[gpu-first] invalid atoms, sel {sel} m1 {m1} {dtype}: {err}", flush=True)
     assert max(err) <= TOL[dtype], err
     assert all(np.isnan(g[~ok]).all() for g in out)
+
+
+@pytest.mark.parametrize("m1,dtype,n", [(100, "f64", 6160), (200, "f64", 1040), (100, "f32", 6160),
+                                        (100, "f32acc64", 6160)])
+def test_infinite_components_stay_infinite(m1, dtype, n):
+    import paper_2107_02103_amd as P
+    x, _ = _quadruples((200,), m1, 16, 3 * m1)
+    rows = np.array([1, 4, 6, 9])                        # full lists; their last slots: first-interval records
+    x.em[rows[0], 199, 1] = np.inf
+    x.em[rows[1], 198, 2] = -np.inf
+    x.em[rows[2], [197, 199], 3] = np.inf, np.inf
+    x.em[rows[3], 190, 1:] = np.inf
+    with np.errstate(all="ignore"):
+        ref = oracle_fwd_bwd(x, rows, dtype)[:2]
+    assert np.isinf(ref[0]).any() and np.isinf(ref[1]).any()
+    c = x.cfg
+    mode = {"f64": P.DPC_F64, "f32": P.DPC_F32, "f32acc64": P.DPC_F32_ACC64}[dtype]
+    op = P.SeATab(x.nets, x.lo, x.L1, x.L2, c.d1, c.d2, c.sel, c.m2, dtype=mode)
+    em, nl, at = (torch.from_numpy(v).cuda().repeat((n // QUADS + 1,) + (1,) * (v.ndim - 1))[:n].contiguous()
+                  for v in (x.em, x.nlist, x.atype))
+    out = [t.cpu().numpy().astype(np.float64) for t in op.forward(em.to(op.t_in), nl, at)]
+    for g, r in zip(out, ref):
+        for k, row in enumerate(rows):
+            got = g[np.arange(n) % QUADS == row]
+            for what in (np.isposinf, np.isneginf, np.isnan):
+                np.testing.assert_array_equal(what(got), np.broadcast_to(what(r[k]), got.shape))
