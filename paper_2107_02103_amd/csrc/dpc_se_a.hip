@@ -147,14 +147,24 @@ __device__ __forceinline__ void locate(const PairRange& P, double x, int& l, dou
   }
 }
 
-// A record that the forward's moments of the first interval may take: t^5 r
-// stays far from overflow.  An infinite or NaN component does not pass: times
-// the polynomial it stays infinite, but t^q times it, summed over coefficients
-// of either sign, would not.
+// A record that the forward's moments of the first interval may take (t^5
+// stays far from overflow).
+__device__ __forceinline__ bool first_interval(int l, double t) { return l == 0 && fabs(t) < 1e8; }
+
+// The components x, y, z of a row as large as 1e199 (float32: 1e36), infinite
+// or NaN; compared as bits.
 template <typename TI>
-__device__ __forceinline__ bool first_interval(int l, double t, const TI (&r)[4]) {
-  const TI big = sizeof(TI) == 8 ? (TI)1e200 : (TI)1e38;
-  return l == 0 && fabs(t) < 1e8 && fabs(r[1]) < big && fabs(r[2]) < big && fabs(r[3]) < big;
+__device__ __forceinline__ bool huge_row(const TI (&r)[4]) {
+  uint32_t top = 0;
+#pragma unroll
+  for (int k = 1; k < 4; ++k) {
+    uint32_t u;
+    if constexpr (sizeof(TI) == 8) u = (uint32_t)(__builtin_bit_cast(uint64_t, r[k]) >> 32);
+    else u = __builtin_bit_cast(uint32_t, r[k]);
+    u &= 0x7fffffffu;
+    top = u > top ? u : top;
+  }
+  return top >= (sizeof(TI) == 8 ? 0x69400000u : 0x7b400000u);
 }
 
 __device__ __forceinline__ void wave_sync() {
@@ -508,7 +518,7 @@ __device__ __forceinline__ Tables build_chunk_set(const Geo& g, const int (&ai)[
       locate(P, (double)rec.r[0], l, rec.t, cl);
       rec.pad = 0.0;
       key = (blk << kOffBits) | (kOffMask - (P.offset + l * 6 * g.ld));
-      if (drop_first && first_interval<TI>(l, rec.t, rec.r)) valid = false;
+      if (drop_first && first_interval(l, rec.t)) valid = false;
       // beyond the table the derivative term vanishes: a zero row removes it
       // (a NaN or infinite x keeps its row, so that it propagates)
       if (kBwd && cl && isfinite(rec.r[0])) {
@@ -646,6 +656,20 @@ __host__ __device__ constexpr size_t fwd_wave_bytes(int m1) {
 // those that held nothing else.
 constexpr int kTakeMin = 12, kTakeLen = 128;
 
+// Whether a forward of NB atoms per wavefront takes moments.  Only then does it
+// run the kernel that has their code; in one kernel for all lists both sides
+// paid (float64, M1 = 100, several types: 24 KB of code and a spilled register,
+// now 21 with and 18 without, neither spills; cu1m, which takes them, 15,140 / 15,060 us).
+// float32 with four channels per lane fits twice as many wavefronts without
+// them (M1 = 200, 10,125 atoms with 40 neighbours: 226 us with, 163 without).
+template <int NB>
+bool wants_moments(const Geo& g) {
+  if (g.nnei > kWindow / NB) return false;       // the list is looked at as one window
+  for (int b = 0; b < g.ntypes; ++b)
+    if (g.blk_end[b] - (b == 0 ? 0 : g.blk_end[b - 1]) >= kTakeLen) return true;
+  return false;
+}
+
 template <typename TI, typename TA, int CPL, bool kOne>
 __device__ __forceinline__ uint32_t first_interval_moments(
     const Geo& g, const WaveAtoms<4>& wa, const int (&ai)[4], int atom, uint32_t vm, uint32_t& occ,
@@ -684,10 +708,13 @@ __device__ __forceinline__ uint32_t first_interval_moments(
         int l;
         bool cl;
         locate(P, (double)r[0], l, t, cl);
-        hit = first_interval<TI>(l, t, r);
+        hit = first_interval(l, t);
       }
       const uint64_t mh = __ballot(hit);
       if (__popcll(mh) < kTakeMin) break;
+      // infinity times the polynomial is infinite; t^q times it, summed over
+      // coefficients of either sign, would not be: such a set stays with the runs
+      if (__ballot(hit && huge_row(r))) break;
       taken |= 1u << c;
       if (mh == __ballot(valid)) occ &= ~(1u << c);
       any = true;
@@ -745,7 +772,8 @@ __device__ __forceinline__ uint32_t first_interval_moments(
 // lane, 205 so.  Float32 coefficients leave two and three wavefronts per SIMD
 // also with four channels per lane (mixed, M1 = 256, 32,000 Al-Cu-Mg atoms:
 // 820 us, 905 with halves), so those modes keep them.
-template <typename TI, typename TA, int CPL, int NB, bool kOne, int kSplit = 1, int kHalves = 1>
+template <typename TI, typename TA, int CPL, int NB, bool kOne, int kSplit = 1, int kHalves = 1,
+          bool kMoments = false>
 // up to 128 channels: registers capped so that 3 wavefronts fit on a SIMD
 __global__ __launch_bounds__(64 * (kSplit > 1 ? kSplit : kWaves))
 __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
@@ -816,7 +844,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
   const int nch = (nnei + kC - 1) / kC;
   int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
-  int turn = 0, wbase = -1;
+  int turn = 0, wbase = kMoments ? 0 : -1;
   RecordShare<kSplit> share;
   if constexpr (kShared && NB == 1) {
     if (nnei <= kWindow) {
@@ -827,11 +855,9 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
     }
   }
   uint32_t taken = 0;          // chunk sets whose first-interval records the moments have taken
-  // (float32 with four channels per lane fits twice as many wavefronts without them:
-  // M1 = 200, 10,125 atoms with 40 neighbours 226 us with, 163 without)
-  if constexpr (NB == 4 && !kShared && !(CPL == 4 && sizeof(TA) == 4)) {
-    if (wa.idx[0] >= 0 && nnei <= kWindow / NB) {
-      wbase = 0;
+  if constexpr (kMoments) {
+    static_assert(!kShared, "a wavefront's own atoms");
+    if (wa.idx[0] >= 0) {      // (the list fits one window: wants_moments)
       vm = valid_window<NB>(g, wa, 0, nlist, lane);
       occ = occupied_chunks<NB>(vm);
       taken = first_interval_moments<TI, TA, CPL, kOne>(g, wa, ai, my_atom, vm, occ, em, W, rs, ld, voff, active,
@@ -839,7 +865,8 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_fwd_kernel(
     }
   }
   for (int cc = kHalves > 1 && wa.idx[0] < 0 ? nch : 0; cc < nch; ++cc, s0 = s0 + kC < nnei ? s0 + kC : 0) {
-    if (s0 - s0 % (kWindow / NB) != wbase) {  // window of nlist signs holding s0
+    // window of nlist signs holding s0 (with moments: the only one, read above)
+    if (!kMoments && s0 - s0 % (kWindow / NB) != wbase) {
       wbase = s0 - s0 % (kWindow / NB);
       vm = valid_window<NB>(g, wa, wbase, nlist, lane);
       occ = occupied_chunks<NB>(vm);
@@ -1873,17 +1900,27 @@ int launch_fwd_split(hipStream_t s, const Geo& g, const void* coeff, const int* 
     hipLaunchKernelGGL(kern, grid, block, shm, s, g, (const TI*)coeff, atype, nlist,
                        (const TI*)em, (TA*)T, (TA*)D);
   };
+  auto with = [&](auto cpl) {
+    constexpr int kC = decltype(cpl)::value;
+    if constexpr (NB == 4 && kSplit == 1 && !(kC == 4 && sizeof(TA) == 4)) {
+      if (wants_moments<NB>(g)) {
+        g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, kC, NB, true, 1, kHalves, true>)
+                      : go(se_a_fwd_kernel<TI, TA, kC, NB, false, 1, kHalves, true>);
+        return;
+      }
+    }
+    g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, kC, NB, true, kSplit, kHalves>)
+                  : go(se_a_fwd_kernel<TI, TA, kC, NB, false, kSplit, kHalves>);
+  };
   if constexpr (kHalves > 1) {
-    g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 2, NB, true, 1, 2>) : go(se_a_fwd_kernel<TI, TA, 2, NB, false, 1, 2>);
+    with(std::integral_constant<int, 2>{});
   } else {
     switch (channels_per_lane(g.m1)) {
-      case 1: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 1, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 1, NB, false, kSplit>); break;
-      case 2: g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 2, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 2, NB, false, kSplit>); break;
+      case 1: with(std::integral_constant<int, 1>{}); break;
+      case 2: with(std::integral_constant<int, 2>{}); break;
       default:
         // (float64: four channels per lane only where wavefronts share atoms)
-        if constexpr (kSplit > 1 || sizeof(TI) == 4) {
-          g.ntypes == 1 ? go(se_a_fwd_kernel<TI, TA, 4, NB, true, kSplit>) : go(se_a_fwd_kernel<TI, TA, 4, NB, false, kSplit>);
-        }
+        if constexpr (kSplit > 1 || sizeof(TI) == 4) with(std::integral_constant<int, 4>{});
         break;
     }
   }
