@@ -628,11 +628,10 @@ def main():
     step_s = wall / args.steps
     peak = PEAK_TFLOPS[dtype]
     tflops = (flop_fwd + flop_bwd) / step_s / 1e12
-    # backward passes that accumulate in float64 (float64 and the mixed mode)
-    # with M1 <= 128 run on the matrix-core kernel (the library's rule), in
-    # float64 MFMA: its peak is the FP64 matrix peak, 78.6 TFLOP/s, as the
-    # FP64 vector peak
-    bwd_mfma = dtype == "f64" or (dtype == "f32acc64" and cfg.widths[-1] <= 160)
+    # the float64 backward, and the mixed mode's with M1 <= 208, run on the
+    # matrix-core kernel (the library's rule), in float64 MFMA: its peak is the
+    # FP64 matrix peak, 78.6 TFLOP/s, as the FP64 vector peak
+    bwd_mfma = dtype == "f64" or (dtype == "f32acc64" and cfg.widths[-1] <= 208)
     bwd_name = "se_a_bwd_mfma_kernel" if bwd_mfma else "se_a_bwd_kernel"
     dom = bwd_name if bwd_ms >= fwd_ms else "se_a_fwd_kernel"
     bound = "mfma" if dom == "se_a_bwd_mfma_kernel" else "alu"

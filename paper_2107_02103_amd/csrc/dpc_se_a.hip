@@ -2044,12 +2044,15 @@ int launch_bwd_vec(hipStream_t s, const Geo& g, const void* coeff, const int* at
 }
 
 // The mixed mode with many channels: the matrix-core kernel pays for whole
-// 16-channel steps and for two wavefronts per SIMD, which short lists (few
-// records per run) and the widest nets do not return.  us, matrix cores /
-// vector ALUs, unsplit: M1 = 129, 10,125 atoms of 138 slots 259 / 271; M1 = 200,
-// 12,288 of 138 328 / 311, 16,384 of 420 532 / 601; M1 = 256, 24,000 of 138
-// 668 / 608, 32,000 of 420 1,201 / 1,186.
-inline bool mixed_on_vector_alus(const Geo& g) { return g.m1 > 208 || (g.m1 > 160 && g.nnei <= 256); }
+// 16-channel steps and for two wavefronts per SIMD, which the widest nets do
+// not return.  The two kernels differ in arithmetic (the vector one evaluates
+// the polynomial in float32), so the line depends on the width alone and not
+// on the list.  us, matrix cores / vector ALUs: M1 = 161, 12,288 atoms of 138
+// slots 289 / 328, 24,000: 498 / 587; M1 = 208: 322 / 340, 551 / 608, 1,536 atoms
+// 63 / 56; M1 = 256, 12,288: 374 / 343, 41,472: 1,152 / 1,041, 32,000 of 420 slots
+// 1,138 / 1,171.  In lists of 40 slots the vector kernel would win from M1 = 161
+// on (200: 4,000 atoms 57 / 44, 10,976 136 / 117).
+inline bool mixed_on_vector_alus(const Geo& g) { return g.m1 > 208; }
 
 template <typename TI, typename TA>
 int launch_bwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
