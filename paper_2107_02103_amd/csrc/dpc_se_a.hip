@@ -1869,19 +1869,34 @@ int make_geo(int nloc, int ntypes, const int* sel, int m1, int m2, const dpc_ran
 // one serial chain of runs, which is what a small system waits for (256 atoms
 // are 64 wavefronts on 1,024 SIMDs).  kBySet: the workgroup's wavefronts take
 // the chunk sets of a few atoms in turn.  kByRun: each takes its share of the
-// runs of one atom.  Both fetch more coefficients per atom.  `run_max` and
-// `set_max` are the atom counts up to which they win (us per call, unsplit /
-// kBySet / kByRun, M1 = 100, float64 unless noted):
-//   forward    256: 67 / 33 / 16    1,372: 70 / 38 / 32    2,048: 70 / 40 / 42    4,000: 76 / 73 / 89    6,912: 90 / 109 / 146
-//   float32    2,048: - / 34 / 28    4,000: - / 42 / 50
-//   matrix bwd 256: 69 / 32 / 16    1,372: 72 / 39 / 34    2,048: - / 42 / 45    4,000: 77 / 76 / 85    6,912: 104 / 112 / 142
-//   vector bwd (float32) 256: 48 / 25 / 16    864: 50 / 29 / 22    2,048: 52 / 52 / 35    4,000: 61 / 86 / 63;
-//     lists of 40 neighbours 3,000: 70 / 63 / 56    5,184: 83 / 106 / 92
-//   forward, M1 = 200    500: 69 / 47 / 36    864: 75 / 47 / 58    1,372: 83 / 92 / 101
-// (lists of 77 neighbours; with 180, kBySet wins up to about 10,000 atoms).
+// runs of one atom.  Both fetch more coefficients per atom, and a list of few
+// chunk sets leaves kBySet little to share; so the atom counts up to which
+// they win depend on the length of the list (us per call, unsplit / kBySet /
+// kByRun, M1 = 100, float64 unless noted, lists of 40, 128 and 512 slots):
+//   forward     1,372:  36 / 31 / 25    67 / 40 / 33   129 / 56 / 48
+//               2,916:  37 / 34 / 45    69 / 47 / 64   132 / 72 / 89
+//               4,000:  39 / 58 / 59    71 / 76 / 84   134 / 105 / 117
+//               5,324:  47 / 62 / 78    79 / 85 / 107  149 / 129 / 153
+//   matrix bwd  1,372:  34 / 32 / 24    70 / 42 / 37   126 / 66 / 59
+//               4,000:  35 / 58 / 57    73 / 80 / 91   128 / 120 / 148
+//               5,324:  44 / 67 / 74    94 / 92 / 114  170 / 150 / 194
+//     from dE/dD 4,000: 76 / 84 / 79   110 / 103 / 108 167 / 146 / 160
+//   float32 fwd 4,000:  36 / 33 / 40    65 / 42 / 50   128 / 63 / 73
+//               5,324:  39 / 55 / 51    71 / 69 / 65   132 / 101 / 94
 enum class Split { kNone, kBySet, kByRun };
-Split split_of(int nloc, int run_max, int set_max) {
-  return nloc <= run_max ? Split::kByRun : (nloc <= set_max ? Split::kBySet : Split::kNone);
+enum { kShort, kMiddle, kLong };       // fewer than 64 slots, fewer than 256, more
+int length_class(const Geo& g) { return g.nnei < 64 ? kShort : (g.nnei < 256 ? kMiddle : kLong); }
+Split split_of(const Geo& g, int run_max, int set_max) {
+  return g.nloc <= run_max ? Split::kByRun : (g.nloc <= set_max ? Split::kBySet : Split::kNone);
+}
+
+// Up to 128 channels.  kBySet wins while its wavefronts (one per atom) all fit
+// at once, `waves` per SIMD; in a second round of them, up to 6,144 atoms, it
+// wins with lists from `second` on, and with middle ones past 4,096 atoms,
+// where the unsplit kernel starts a second wavefront per SIMD.
+Split split_narrow(const Geo& g, int run_max, int waves, int second) {
+  const bool again = length_class(g) >= second || (length_class(g) == kMiddle && g.nloc > 4096);
+  return split_of(g, run_max, again ? 6144 : 1024 * waves);
 }
 
 // Channels per lane: 1 (m1 <= 64), 2 (m1 <= 128) or 4 (m1 <= 256).
@@ -1931,8 +1946,10 @@ template <typename TI, typename TA>
 int launch_fwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype, const int* nlist,
                const void* em, void* T, void* D) {
   // more than 128 channels: fewer wavefronts fit at once with four channels per lane
-  switch (g.m1 <= 128 ? split_of(g.nloc, sizeof(TI) == 8 ? 1536 : 2048, 6144)
-                       : split_of(g.nloc, 512, sizeof(TI) == 8 ? 1024 : 2048)) {
+  // (M1 = 200, float64, 128 slots, 500: 67 / 47 / 33, 864: 67 / 49 / 60, 1,372: 68 / 91 / 89)
+  switch (g.m1 <= 128 ? split_narrow(g, sizeof(TI) == 8 ? 1536 : 2048, g.m1 <= 64 || sizeof(TA) == 4 ? 4 : 3,
+                                      sizeof(TA) == 4 ? kMiddle : kLong)
+                       : split_of(g, 512, sizeof(TI) == 8 ? 1024 : 2048)) {
     case Split::kByRun: return launch_fwd_split<TI, TA, 1, 8>(s, g, coeff, atype, nlist, em, T, D);
     case Split::kBySet: return launch_fwd_split<TI, TA, DPC_FWD_ATOMS_PER_WAVE, 4>(s, g, coeff, atype, nlist, em, T, D);
     default:
@@ -2003,11 +2020,17 @@ template <typename TI, typename TO, bool kFromD = false>
 int launch_bwd_mfma(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
                     const int* nlist, const void* em, const void* dT, void* dR,
                     const double* Tin = nullptr, const double* dD = nullptr) {
-  // above 128 channels (S > 8), us unsplit / kBySet / kByRun: float64 256: 94 / 45 / 20, 1,372:
-  // 109 / 62 / 56, 2,048: 109 / 64 / 74, 4,000: 109 / 117 / 133; mixed 5,184: 197 / - / 152, 8,788: 430 / - / 323, 16,384: 532 / - / 585
-  const bool wide = g.m1 > 16 * kMfmaWide;
-  switch (!wide ? split_of(g.nloc, 1280, 6144)
-                : (sizeof(TI) == 4 ? split_of(g.nloc, 10240, 10240) : split_of(g.nloc, 1536, 3072))) {
+  // above 128 channels (S > 8), us unsplit / kBySet / kByRun, M1 = 200, lists of 40
+  // and 128 slots: float64 1,372: 45 / 44 / 28, 96 / 59 / 57, 2,048: 46 / 45 / 38, 96 / 60 / 76, 2,916:
+  // 47 / 80 / 52, 97 / 93 / 107; mixed 5,324: 77 / - / 75, 150 / - / 142, 6,912: 80 / - / 100,
+  // 151 / - / 183, 8,788: 131 / - / 120, 239 / - / 224, 10,976: - , 243 / - / 271
+  const bool wide = g.m1 > 16 * kMfmaWide, brief = length_class(g) == kShort;
+  // (the prologue from dE/dD is shared too)
+  Split split = split_narrow(g, 1280, 3, kFromD ? kMiddle : kLong);
+  if (wide) split = sizeof(TI) == 8 ? split_of(g, brief ? 2048 : 1536, brief ? 2048 : 3072)
+                                    // (unsplit, two wavefronts per SIMD hold 8,192 atoms; short lists then win)
+                                    : split_of(g, brief && g.nloc <= 8192 ? 6144 : 10240, 0);
+  switch (split) {
     case Split::kByRun: return launch_mfma_split<TI, TO, kFromD, 1, 8>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
     case Split::kBySet: return launch_mfma_split<TI, TO, kFromD, kMfmaAtoms, 4>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
     default: return launch_mfma_split<TI, TO, kFromD, kMfmaAtoms, 1>(s, g, coeff, atype, nlist, em, dT, dR, Tin, dD);
@@ -2061,20 +2084,26 @@ int launch_bwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
   if constexpr (sizeof(TA) == 8) {
     if constexpr (sizeof(TI) == 4) {
       if (mixed_on_vector_alus(g)) {
-        // (us unsplit / kByRun, M1 = 256, 138 slots: 1,536: 86 / 55, 6,591: 211 / 195, 10,125: 294 / 313)
-        return g.nloc <= 8192 ? launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR)
-                               : launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
+        // (us unsplit / kByRun, M1 = 256, 40, 128 and 512 slots: 500: 27 / 18, -, -; 1,372: 28 / 28,
+        // 71 / 49, -; 2,916: 40 / 52, 99 / 89, 197 / 163; 6,912: 78 / 119, 180 / 188, 370 / 334)
+        constexpr int run_max[] = {1024, 3072, 8192};
+        return split_of(g, run_max[length_class(g)], 0) == Split::kByRun
+                   ? launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR)
+                   : launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
       }
     }
     // the rest of float64 and the mixed mode (float64 accumulation) on the matrix cores
     return launch_bwd_mfma<TI, TA>(s, g, coeff, atype, nlist, em, dT, dR);
   } else {
-    // the float32 mode keeps float32 arithmetic on the vector ALUs
-    switch (g.m1 <= 128 ? split_of(g.nloc, 3072, 3072) : split_of(g.nloc, 640, 1536)) {
-      case Split::kByRun: return launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR);
-      case Split::kBySet: return launch_bwd_vec<TI, TA, NB, 4>(s, g, coeff, atype, nlist, em, dT, dR);
-      default: return launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
-    }
+    // the float32 mode keeps float32 arithmetic on the vector ALUs; kBySet never
+    // wins there (us unsplit / kBySet / kByRun, 40, 128 and 512 slots, M1 = 100: 1,372:
+    // 20 / 24 / 17, 51 / 35 / 28, 105 / 55 / 52; 2,916: 24 / 44 / 30, 58 / 63 / 50, 116 / 100 / 92;
+    // M1 = 200: 1,372: 25 / 33 / 24, 65 / 48 / 41, 130 / 76 / 72; 2,916: 33 / 59 / 45, 77 / 88 / 77,
+    // 153 / 139 / 130)
+    const int run_max[] = {1536, g.m1 <= 128 ? 3072 : 2048, 3072};
+    return split_of(g, run_max[length_class(g)], 0) == Split::kByRun
+               ? launch_bwd_vec<TI, TA, 1, 4>(s, g, coeff, atype, nlist, em, dT, dR)
+               : launch_bwd_vec<TI, TA, NB, 1>(s, g, coeff, atype, nlist, em, dT, dR);
   }
 }
 

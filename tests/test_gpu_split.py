@@ -72,3 +72,30 @@ def test_from_dD_in_every_mapping():
             err = normwise(got, ref[np.arange(n) % BASE])
             print(f"[gpu-split] from dD, m1 {m1} n {n}: {err:.2e}", flush=True)
             assert err <= TOL["f64"], (m1, n, err)
+
+
+@pytest.mark.parametrize("sel,m1,dtype", [((63,), 100, "f64"), ((64,), 60, "f64"), ((200, 55), 100, "f64"),
+                                          ((256,), 100, "f64"), ((63,), 100, "f32"), ((64,), 100, "f32"),
+                                          ((40,), 200, "f64"), ((40,), 200, "f32acc64"), ((40,), 256, "f32acc64"),
+                                          ((90,), 256, "f32acc64"), ((40, 20), 60, "f32acc64"), ((90,), 200, "f32")])
+def test_sharing_by_the_length_of_the_list(sel, m1, dtype):
+    # both sides of the atom counts at which short, middle and long lists change how atoms are shared
+    import paper_2107_02103_amd as P
+    x = edge_inputs(BASE, sel, m1, 8, seed=sum(sel) + m1)
+    good = np.array([i for i in range(BASE) if i != BAD])
+    ref = oracle_fwd_bwd(x, good, dtype)
+    x.atype[BAD] = -1
+    c = x.cfg
+    mode = {"f64": P.DPC_F64, "f32": P.DPC_F32, "f32acc64": P.DPC_F32_ACC64}[dtype]
+    op = P.SeATab(x.nets, x.lo, x.L1, x.L2, c.d1, c.d2, c.sel, c.m2, dtype=mode)
+    base = [torch.from_numpy(v).cuda() for v in (x.em, x.nlist, x.atype, x.dT)]
+    for k in (0, 3):
+        base[k] = base[k].to(op.t_in)
+    for n in (1024, 1025, 1536, 1537, 2048, 2049, 3072, 3073, 4096, 4097, 6144, 6145, 8192, 8193):
+        em, nl, at, dT = (t.repeat((n // BASE + 1,) + (1,) * (t.dim() - 1))[:n].contiguous() for t in base)
+        out = (*op.forward(em, nl, at), op.backward(em, nl, at, dT))
+        out = [t.cpu().numpy().astype(np.float64) for t in out]
+        rows = np.arange(n) % BASE
+        err = [normwise(g[rows != BAD], r[np.searchsorted(good, rows[rows != BAD])]) for g, r in zip(out, ref)]
+        assert max(err) <= TOL[dtype], (n, err)
+        assert all(np.isnan(g[rows == BAD]).all() for g in out)
