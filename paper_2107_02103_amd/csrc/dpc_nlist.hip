@@ -34,7 +34,7 @@ namespace {
 
 constexpr int kNlWaves = 4;      // wavefronts (atoms) per workgroup of the list kernel
 constexpr int kNlCap = 1024;     // neighbours within rc an atom may have
-constexpr int kNlKeep = 512;     // of these, what one wavefront's own LDS holds
+constexpr int kNlKeep = 512;     // of these, what a wavefront's LDS holds in systems with fewer
 constexpr int kScanThreads = 1024;
 
 struct alignas(16) NlAtom {      // an atom in cell order
@@ -254,7 +254,7 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-constexpr int kNlPer = kNlKeep / 64, kNlBuckets = 256;
+constexpr int kNlBuckets = 256;
 
 // One wavefront per atom.  Both halves are bound by vector issue.
 //   Candidates: the atoms of the 27 cells, 64 at a time.  Their periodic
@@ -267,18 +267,20 @@ constexpr int kNlPer = kNlKeep / 64, kNlBuckets = 256;
 // type), the buckets' starts are summed over the lanes, each neighbour moves
 // to its bucket, and its rank inside the bucket (one or two neighbours; a
 // whole shell in a perfect crystal) comes from comparing with the bucket only.
-//   An atom with more neighbours than a wavefront's own LDS holds is done
-// after the others of its workgroup, with all of the workgroup's LDS: so 20
-// wavefronts share a CU and not 12.
-template <bool kOne>
-__global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(5))) void nl_list_kernel(
+//   kKeep neighbours per atom fit the wavefront's own LDS: 512, so that 20
+// wavefronts share a CU and not 12, or all 1,024 where more than 512 are
+// expected (long_lists).  An atom with more than kKeep is done after the others
+// of its workgroup, with all of the workgroup's LDS.
+template <bool kOne, int kKeep>
+__global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(kKeep > kNlKeep ? 3 : 5))) void nl_list_kernel(
     const NlGeo g, const double* __restrict__ coord, const int* __restrict__ cell_of,
     const int* __restrict__ start, const NlAtom* __restrict__ sorted, int* __restrict__ nlist,
     int* __restrict__ status) {
 #pragma clang fp contract(off)
-  static_assert(kNlWaves * kNlKeep >= kNlCap + 4, "the workgroup's LDS holds one long list");
-  __shared__ uint64_t cand_r2[kNlWaves * kNlKeep];
-  __shared__ uint32_t cand_jt[kNlWaves * kNlKeep];
+  static_assert(kNlWaves * kKeep >= kNlCap + 4, "the workgroup's LDS holds one long list");
+  constexpr int kNlPer = kKeep / 64;
+  __shared__ uint64_t cand_r2[kNlWaves * kKeep];
+  __shared__ uint32_t cand_jt[kNlWaves * kKeep];
   __shared__ uint32_t buckets[kNlWaves][kNlBuckets];
   __shared__ int longer[kNlWaves];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -286,8 +288,8 @@ __global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(5
   const bool active = (int)(blockIdx.x * kNlWaves) + wave < g.nloc;
   // past the last atom: the last one again, for the barriers' sake; nothing is written
   const int i = active ? (int)(blockIdx.x * kNlWaves) + wave : g.nloc - 1;
-  uint64_t* my_r2 = cand_r2 + wave * kNlKeep;
-  uint32_t* my_jt = cand_jt + wave * kNlKeep;
+  uint64_t* my_r2 = cand_r2 + wave * kKeep;
+  uint32_t* my_jt = cand_jt + wave * kKeep;
   const double xi = coord[3 * (size_t)i], yi = coord[3 * (size_t)i + 1], zi = coord[3 * (size_t)i + 2];
   const int ci = __builtin_amdgcn_readfirstlane(cell_of[i]);
   const int cx = ci / (g.nc * g.nc), cy = (ci / g.nc) % g.nc, cz = ci % g.nc;
@@ -382,12 +384,12 @@ __global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(5
     }
     return n;
   };
-  const int n = active ? collect(kNlKeep) : 0;
+  const int n = active ? collect(kKeep) : 0;
   const int m = n < kNlCap ? n : kNlCap;
   int* row = nlist + (size_t)i * g.nnei;
 
   int cntv = 0;                   // lane t: neighbours of type t (all of them, before truncation)
-  if (m <= kNlKeep) {
+  if (kKeep >= kNlCap || m <= kKeep) {
     uint32_t* hist = buckets[wave];
 #pragma unroll
     for (int q = 0; q < kNlBuckets / 64; ++q) hist[64 * q + lane] = 0;
@@ -396,17 +398,22 @@ __global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(5
     int bk[kNlPer], ar[kNlPer];   // bucket, and order of arrival in it
     wave_sync();
     const int nu = (m + 63) >> 6;
+    constexpr bool kReread = kKeep > kNlKeep;    // too many neighbours per lane to hold them all
+    // equal r2 share a bucket, larger r2 never come in an earlier one
+    auto bucket = [&](uint64_t v, uint32_t w) __attribute__((always_inline)) {
+      int b = min((int)(__builtin_bit_cast(double, v) * g.bucket_scale), g.type_buckets - 1);
+      if (!kOne) b += (int)(w >> kJBits) * g.type_buckets;
+      return b;
+    };
 #pragma unroll
     for (int u = 0; u < kNlPer; ++u) {
-      if (u >= nu) break;
+      if (kReread ? false : u >= nu) break;      // (sixteen of them: the compiler unrolls no loop with a break)
       const int q = 64 * u + lane;
       r2[u] = my_r2[q];
       jt[u] = my_jt[q];
       bk[u] = ar[u] = 0;
       if (q < m) {
-        // equal r2 share a bucket, larger r2 never come in an earlier one
-        bk[u] = min((int)(__builtin_bit_cast(double, r2[u]) * g.bucket_scale), g.type_buckets - 1);
-        if (!kOne) bk[u] += (int)(jt[u] >> kJBits) * g.type_buckets;
+        bk[u] = bucket(r2[u], jt[u]);
         ar[u] = (int)atomicAdd(&hist[bk[u]], 1u);
       }
     }
@@ -423,46 +430,66 @@ __global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(5
     // lane t: first rank of type t among all neighbours (m past the last type)
     const int firstv = lane < ntypes ? (int)hist[lane * g.type_buckets] : m;
     cntv = __builtin_amdgcn_ds_bpermute((lane + 1) << 2, firstv) - firstv;
+    auto ends = [&](int b, int& lo, int& hi) __attribute__((always_inline)) {
+      lo = (int)hist[b];
+      hi = b + 1 < kNlBuckets ? (int)hist[b + 1] : m;
+    };
+    // a neighbour's slot from its rank inside its bucket [lo, hi)
+    auto place = [&](bool in, uint64_t v, uint32_t w, int lo, int hi) __attribute__((always_inline)) {
+      int rank = lo;
+      for (int e = lo; __ballot(e < hi); ++e) {
+        if (e < hi) {
+          const uint64_t o = my_r2[e];
+          // one type per bucket: (r2, j) decides
+          rank += o < v || (o == v && my_jt[e] < w) ? 1 : 0;
+        }
+      }
+      int to = rank, end = g.sel[0];       // the slot, and the end of its block
+      if constexpr (!kOne) {
+        const int t = (int)(w >> kJBits);
+        for (int u = 0; u < ntypes; ++u) {
+          const int shift_u = g.blk[u] - __builtin_amdgcn_readlane(firstv, u);
+          to = u == t ? rank + shift_u : to;
+          end = u == t ? g.blk[u + 1] : end;
+        }
+      }
+      if (in && to < end) row[to] = (int)(w & kJMask);
+    };
     int lo[kNlPer], hi[kNlPer];
 #pragma unroll
     for (int u = 0; u < kNlPer; ++u) {
-      if (u >= nu) break;
+      if (kReread ? false : u >= nu) break;
       lo[u] = hi[u] = 0;
       if (64 * u + lane < m) {
-        lo[u] = (int)hist[bk[u]];
-        hi[u] = bk[u] + 1 < kNlBuckets ? (int)hist[bk[u] + 1] : m;
+        ends(bk[u], lo[u], hi[u]);
         my_r2[lo[u] + ar[u]] = r2[u];
         my_jt[lo[u] + ar[u]] = jt[u];
       }
     }
     wave_sync();
+    if constexpr (kReread) {
+#pragma unroll 1
+      for (int q = lane; q - lane < m; q += 64) {
+        const uint64_t v = my_r2[q];
+        const uint32_t w = my_jt[q];
+        int l = 0, h = 0;
+        if (q < m) ends(bucket(v, w), l, h);
+        place(q < m, v, w, l, h);
+      }
+    } else {
 #pragma unroll
-    for (int u = 0; u < kNlPer; ++u) {
-      if (u >= nu) break;
-      int rank = lo[u];
-      for (int e = lo[u]; __ballot(e < hi[u]); ++e) {
-        if (e < hi[u]) {
-          const uint64_t o = my_r2[e];
-          // one type per bucket: (r2, j) decides
-          rank += o < r2[u] || (o == r2[u] && my_jt[e] < jt[u]) ? 1 : 0;
-        }
+      for (int u = 0; u < kNlPer; ++u) {
+        if (u >= nu) break;
+        place(64 * u + lane < m, r2[u], jt[u], lo[u], hi[u]);
       }
-      int to = rank, end = g.sel[0];       // the slot, and the end of its block
-      if constexpr (!kOne) {
-        const int t = (int)(jt[u] >> kJBits);
-        for (int v = 0; v < ntypes; ++v) {
-          const int shift_v = g.blk[v] - __builtin_amdgcn_readlane(firstv, v);
-          to = v == t ? rank + shift_v : to;
-          end = v == t ? g.blk[v + 1] : end;
-        }
-      }
-      if (64 * u + lane < m && to < end) row[to] = (int)(jt[u] & kJMask);
     }
   }
   // lists that did not fit: one wavefront after the other, in all of the LDS
-  if (lane == 0) longer[wave] = m > kNlKeep;
-  __syncthreads();
-  for (int w = 0; w < kNlWaves; ++w) {
+  if constexpr (kKeep < kNlCap) {
+    if (lane == 0) longer[wave] = m > kKeep;
+    __syncthreads();
+  }
+  for (int w = 0; w < (kKeep < kNlCap ? kNlWaves : 0); ++w) {
     if (!longer[w]) continue;              // the same for every thread
     __syncthreads();
     if (w != wave) continue;
@@ -542,6 +569,18 @@ __global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(5
     if (__ballot(trunc) && lane == 0) atomicAdd(status, 1);
     if (n > kNlCap && lane == 0) atomicAdd(status + 1, 1);
   }
+}
+
+// Whether atoms with more than kNlKeep neighbours are to be expected: by the
+// neighbours of a mean atom, and well below that where more slots are asked for
+// (a slab or a cluster is denser than its box).  us, 512 and 1,024 neighbours in
+// a wavefront's LDS: 16,384 atoms with 531 neighbours 2,421 / 296, 131,072 with
+// 603 20,300 / 2,310, with 464 1,270 / 1,704, with 180 547 / 751; ranking by
+// comparison in a list of 1,024, one wavefront each, took 1,030 and 9,270 for
+// the first two.
+bool long_lists(const NlGeo& g) {
+  const double r = std::sqrt(g.rc2), mean = 4.0 / 3.0 * 3.14159265358979 * g.rc2 * r / (g.box * g.box * g.box) * g.nloc;
+  return mean > (g.nnei > kNlKeep ? kNlKeep / 2 : kNlKeep - 32);
 }
 
 constexpr size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -649,9 +688,12 @@ static int dpc_nlist_launch(void* stream, int nloc, int ntypes, const int* sel, 
     hipLaunchKernelGGL(nl_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, g.ncell, count, start, cursor);
     hipLaunchKernelGGL(nl_scatter_kernel, ga, b256, 0, s, g, coord, atype, cell_of, cursor, sorted);
   }
-  hipLaunchKernelGGL(ntypes == 1 ? nl_list_kernel<true> : nl_list_kernel<false>,
-                     dim3((nloc + kNlWaves - 1) / kNlWaves), dim3(64 * kNlWaves), 0, s, g, coord, cell_of, start,
-                     sorted, nlist, status);
+  auto list = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((nloc + kNlWaves - 1) / kNlWaves), dim3(64 * kNlWaves), 0, s, g, coord, cell_of,
+                       start, sorted, nlist, status);
+  };
+  if (long_lists(g)) list(ntypes == 1 ? nl_list_kernel<true, kNlCap> : nl_list_kernel<false, kNlCap>);
+  else list(ntypes == 1 ? nl_list_kernel<true, kNlKeep> : nl_list_kernel<false, kNlKeep>);
   const int ls = dpc_internal_launch_status();
   if (ls != DPC_OK || !status_host) return ls;
   int h[2] = {0, 0};

@@ -92,6 +92,33 @@ def test_many_neighbours(near):
     _check(x, rng.integers(0, 2, size=len(x)), (400, 500), 40.0, 9.0)
 
 
+@pytest.mark.parametrize("sel", [(900,), (400, 500), (150, 150), (40, 30, 50, 20)])
+@pytest.mark.parametrize("n,edge,cluster", [(1000, 2.01, 0), (3500, 3.02, 0), (1600, 2.2, 800)])
+def test_lists_longer_than_512(n, edge, cluster, sel):
+    # dense systems, ranked through buckets with up to 1,024 neighbours each; in one
+    # a cluster's atoms have more, which the second counter says
+    rc, rng = 3.0, np.random.default_rng(n + len(sel))
+    x = rng.uniform(0, edge * rc, size=(n, 3))
+    x[:cluster] = 0.5 * edge * rc + rng.normal(0, 0.3, size=(cluster, 3))
+    t = np.ascontiguousarray(rng.integers(0, len(sel), size=n), np.int32)
+    _, _, nl, st = _build(x, t, sel, edge * rc, rc)
+    ref, _, over = onl.neighbour_list(x, t, sel, edge * rc, rc)
+    d = x[:, None] - x[None]
+    d -= edge * rc * np.rint(d / (edge * rc))
+    count = ((d ** 2).sum(-1) < rc * rc).sum(1) - 1
+    few = count <= 1024
+    assert (count > 512).any() and st[1] == (~few).sum()
+    assert cluster or st == (over, 0)
+    np.testing.assert_array_equal(nl.cpu().numpy()[few], ref[few])
+
+
+def test_long_lists_of_a_perfect_crystal():
+    # whole shells in one bucket, more than 512 neighbours
+    g = np.stack(np.meshgrid(*[np.arange(12.0)] * 3, indexing="ij"), -1).reshape(-1, 3)
+    _check(g, np.zeros(len(g), int), (600,), 12.0, 5.001)
+    _check(g, np.random.default_rng(1).integers(0, 2, size=len(g)), (300, 320), 12.0, 5.001)
+
+
 @pytest.mark.parametrize("n,box", [(1, 7.0), (8191, 30.0), (8192, 90.0), (8193, 30.0), (700, 200.0)])
 def test_cell_lists_of_one_workgroup_and_of_several(n, box):
     # both sides of the largest system whose cells one workgroup sorts, few and
