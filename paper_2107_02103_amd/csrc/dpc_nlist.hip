@@ -281,7 +281,7 @@ __global__ __launch_bounds__(64 * kNlWaves) __attribute__((amdgpu_waves_per_eu(k
   constexpr int kNlPer = kKeep / 64;
   __shared__ uint64_t cand_r2[kNlWaves * kKeep];
   __shared__ uint32_t cand_jt[kNlWaves * kKeep];
-  __shared__ uint32_t buckets[kNlWaves][kNlBuckets];
+  __shared__ __align__(16) uint32_t buckets[kNlWaves][kNlBuckets];   // read and written 16 bytes at a time
   __shared__ int longer[kNlWaves];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ntypes = kOne ? 1 : g.ntypes;
