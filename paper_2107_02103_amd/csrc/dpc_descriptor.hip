@@ -26,7 +26,7 @@
 namespace {
 
 constexpr int kLanes = 64;
-constexpr size_t kMaxLds = 65536;   // LDS a workgroup may take without opting in
+constexpr size_t kRowsLds = 65536;   // an atom's rows in LDS: what the header allows
 
 // LDS of one wavefront: T [m1][4] and dE/dD [m1][m2 + 1], in the compute type
 template <typename TC>
@@ -224,8 +224,8 @@ int launch_m16(hipStream_t s, int nloc, int m1, const void* T, const void* dD, v
 template <typename TT, typename TO, typename TC>
 int launch(hipStream_t s, int nloc, int m1, int m2, const void* T, const void* dD, void* dT) {
   const size_t wb = wave_bytes<TC>(m1, m2);
-  if (wb > kMaxLds) return DPC_ENOTSUP;
-  const int waves = wb * 4 <= kMaxLds ? 4 : (wb * 2 <= kMaxLds ? 2 : 1);
+  if (wb > kRowsLds) return DPC_ENOTSUP;
+  const int waves = wb * 4 <= kRowsLds ? 4 : (wb * 2 <= kRowsLds ? 2 : 1);
   const dim3 grid((nloc + waves - 1) / waves), block(kLanes * waves);
   (void)hipGetLastError();  // report only what this launch raises
   hipLaunchKernelGGL((descriptor_bwd_kernel<TT, TO, TC>), grid, block, waves * wb, s, nloc, m1, m2,

@@ -628,6 +628,8 @@ __global__ __launch_bounds__(256, 2) void fit_input_grad_kernel(int n, int nin, 
 }
 
 constexpr int kCus = 256;
+template <int N>
+using Int = std::integral_constant<int, N>;
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // The number of workgroups that share an atom group's tiles: a CU's time is
@@ -703,20 +705,20 @@ int fit_240(hipStream_t s, int n, const dpc_fitting_net* net, const double* D, d
     else if (cost(5) <= cost(3)) go(fit_layer1_kernel<5, 32>, 5);
     else go(fit_layer1_kernel<3, 32>, 3);
   }
-  auto middle = [&](auto kern, int mt, int nw) {
-    const size_t lds = (kFw * (16 * mt + 4) + nw * 16 * mt) * sizeof(double);
-    if (lds > 65536)
-      (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)lds);
+  auto middle = [&](auto kern, auto mt_, auto nw_) {
+    constexpr int mt = decltype(mt_)::value, nw = decltype(nw_)::value;
+    constexpr size_t lds = (kFw * (16 * mt + 4) + nw * 16 * mt) * sizeof(double);
+    static_assert(lds <= kMaxLds, "a workgroup's LDS");
     hipLaunchKernelGGL(kern, dim3(ceil_div(n, 16 * mt)), dim3(64 * nw), lds, s, n, t1, net->W[1], net->b[1],
                        net->W[2], net->b[2], net->w_out, net->b_out, E, dD ? dz1 : nullptr);
   };
   // at most one workgroup of 16 atoms per CU: a tile per wavefront (4,096 atoms: 62 us, 85 with 32 atoms)
-  if (n <= 16 * kCus) middle(fit_middle_kernel<1, 16>, 1, 16);
+  if (n <= 16 * kCus) middle(fit_middle_kernel<1, 16>, Int<1>{}, Int<16>{});
   // three atom tiles where they leave fewer of them per CU (12,288 atoms: 256
   // workgroups, 131 us; 384 with two tiles, 163)
-  else if (3 * ceil_div(ceil_div(n, 48), kCus) < 2 * ceil_div(ceil_div(n, 32), kCus)) middle(fit_middle_kernel<3, 16>, 3, 16);
-  else middle(fit_middle_kernel<2, 8>, 2, 8);
+  else if (3 * ceil_div(ceil_div(n, 48), kCus) < 2 * ceil_div(ceil_div(n, 32), kCus))
+    middle(fit_middle_kernel<3, 16>, Int<3>{}, Int<16>{});
+  else middle(fit_middle_kernel<2, 8>, Int<2>{}, Int<8>{});
   if (dD) launch_input_grad(s, n, nin, dz1, net->W[0], dD);
   return dpc_internal_launch_status();
 }

@@ -58,7 +58,6 @@ constexpr int kLanes = 64;
 constexpr int kBatch = 4;      // records per cross-lane reduction in the backward pass
 constexpr int kOffBits = 28;   // keys: (block << 28) | (2^28 - 1 - coefficient offset)
 constexpr int kOffMask = (1 << kOffBits) - 1;
-constexpr size_t kMaxLds = 65536;    // LDS a workgroup may take without opting in
 
 struct PairRange {             // one ordered type pair's table, as the kernels see it
   double lo, d1, d2;
@@ -1979,6 +1978,7 @@ void launch_mfma_s(hipStream_t s, const Geo& g, dim3 grid, const void* coeff,
   };
   constexpr int lo = mfma_slot_kib(S, 16 * S - 12, es);
   static_assert(mfma_slot_kib(S, 16 * S, es) <= lo + 1, "two slot sizes per S");
+  static_assert((split > 1 ? split : kWaves) * bwdm_wave_bytes(S, lo + 1, NB) <= kMaxLds, "a workgroup's LDS");
   // (split workgroups always take the larger slot: latency, not LDS, limits them)
   const bool small = split == 1 && ns <= lo;
   constexpr int hi = lo + 1, sm = split == 1 ? lo : hi;
