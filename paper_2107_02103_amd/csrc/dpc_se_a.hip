@@ -176,10 +176,10 @@ __device__ __forceinline__ void wave_sync() {
 // kGroups * NB consecutive atoms.  With several types it hands them to its wavefronts grouped by type
 // (atoms of an invalid type after the others, index order inside a group),
 // so that the atoms of one wavefront share their tables as often as
-// possible: more records per interval.  An atom's records and sums do not
-// depend on which atoms share its wavefront; only the chunk set its sums
-// start from does (the start rotates with the wavefront), i.e. the order of
-// rounding.  idx[a] is the atom's index, -1 past
+// possible: more records per interval.  Which atoms share a wavefront changes
+// only the rounding of their sums: the chunk set they start from (it rotates
+// with the wavefront), and which records the forward takes as moments of the
+// first interval (a chunk set is taken for all four atoms together).  idx[a] is the atom's index, -1 past
 // nloc (those come last); lane a < NB of `lanes` holds idx[a] as well, for
 // lookups with an index known only at run time (a register array indexed so
 // would go to scratch memory).
@@ -1054,6 +1054,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   constexpr bool kShared = kSplit > 1;
+  static_assert(!kShared || NB == 1, "wavefronts share one atom's runs");
   WaveAtoms<NB> wa;
   if constexpr (kShared) wa = shared_atoms<NB>(g, lane);
   else wa = wave_atoms<NB, kOne>(g, atype, lane, wave);
@@ -1127,9 +1128,9 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
   const int nch = (nnei + kC - 1) / kC;
   int s0 = kShared ? 0 : ((int)(blockIdx.x * 5 + wave * 3) % nch) * kC;
   uint32_t vm = 0, occ = 0;
-  int turn = 0, wbase = -1;
+  int wbase = -1;
   RecordShare<kSplit> share;
-  if constexpr (kShared && NB == 1) {
+  if constexpr (kShared) {
     if (nnei <= kWindow) {
       wbase = 0;
       vm = valid_window<NB>(g, wa, 0, nlist, lane);
@@ -1147,8 +1148,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
       if (!kShared || cc % kSplit == wave) zero_rows<TA, NB>(g, ai, my_atom, s0, dR, lane);
       continue;
     }
-    if (kShared && NB > 1 && turn++ % kSplit != wave) continue;
-    if (kShared && NB == 1 && !share.enter(vm, (s0 - wbase) / kC, wave)) continue;
+    if (kShared && !share.enter(vm, (s0 - wbase) / kC, wave)) continue;
     const Tables tb = build_chunk_set<TI, TA, NB, true, kOne>(g, ai, my_atom, s0, wbase, vm, em, W.z, W.s, lane);
     // Each lane writes the dE/dR~ row of its own slot (zero for padding) after
     // the chunk set's runs: consecutive lanes, consecutive rows, and no store
@@ -1156,13 +1156,13 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
     // Of a chunk set whose runs are shared out, a wavefront writes the records
     // of its runs, [e_lo, e_hi) in merged order; one of them also the padding.
     int r = 0, r1 = tb.nruns, e_lo = 0, e_hi = tb.n;
-    if constexpr (kShared && NB == 1) {
+    if constexpr (kShared) {
       share.runs(tb, lane, r, r1);
       e_lo = readlane(tb.vs, r < kLanes ? r : kLanes - 1);
       e_hi = r1 < kLanes ? readlane(tb.vs, r1) : tb.n;
     }
     auto write_rows = [&]() __attribute__((always_inline)) {
-      if (kShared && NB == 1 && (tb.rank < 0 ? !share.owner() : tb.rank < e_lo || tb.rank >= e_hi)) return;
+      if (kShared && (tb.rank < 0 ? !share.owner() : tb.rank < e_lo || tb.rank >= e_hi)) return;
       if (tb.rank >= -1) {
         TA v[4] = {(TA)0, (TA)0, (TA)0, (TA)0};
         if (tb.rank >= 0) {
@@ -1173,7 +1173,7 @@ __attribute__((amdgpu_waves_per_eu(CPL <= 2 ? 3 : 1))) void se_a_bwd_kernel(
         store_row(dR + ((size_t)my_atom * nnei + s0 + lane % kC) * 4, v);
       }
     };
-    if (tb.n == 0 || (kShared && NB == 1 && r == r1)) {
+    if (tb.n == 0 || (kShared && r == r1)) {
       e_hi = e_lo;            // no records: padding only
       write_rows();
       continue;
@@ -1963,6 +1963,13 @@ int launch_fwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
 // float64 or mixed: the matrix-core kernel, ceil(M1 / 16) K steps
 // per channel block, an interval copied by mfma_slot_kib(S, ld, esize) loads
 // (ld lies in [16 S - 12, 16 S], so that count takes one of two values per S)
+// What the rules below ever ask for: the mixed mode stops at 208 channels, and
+// shares only runs above 128.
+template <typename TI, int S, int NB, int kSplit>
+constexpr bool mfma_wanted() {
+  return sizeof(TI) == 8 || (S <= 13 && (S <= kMfmaWide || kSplit == 1 || NB == 1));
+}
+
 template <typename TI, typename TO, int S, bool kFromD, int NB, int kSplit>
 void launch_mfma_s(hipStream_t s, const Geo& g, dim3 grid, const void* coeff,
                    const int* atype, const int* nlist, const void* em, const void* dT, void* dR,
@@ -1999,13 +2006,15 @@ int launch_mfma_split(hipStream_t s, const Geo& g, const void* coeff, const int*
   constexpr int atoms = kSplit > 1 ? NB : kWaves * NB;
   const dim3 grid((g.nloc + atoms - 1) / atoms);
   (void)hipGetLastError();  // report only what this launch raises
-#define DPC_CASE(n)                                                                                   \
-  case n:                                                                                             \
-    launch_mfma_s<TI, TO, n, kFromD, NB, kSplit>(s, g, grid, coeff, atype, nlist, em, dT, dR, Tin, dD); \
+#define DPC_CASE(n)                                                                                       \
+  case n:                                                                                                 \
+    if constexpr (mfma_wanted<TI, n, NB, kSplit>())                                                       \
+      launch_mfma_s<TI, TO, n, kFromD, NB, kSplit>(s, g, grid, coeff, atype, nlist, em, dT, dR, Tin, dD); \
+    else                                                                                                  \
+      return DPC_ENOTSUP;                                                                                 \
     break;
   switch (S) {
     DPC_CASE(1) DPC_CASE(2) DPC_CASE(3) DPC_CASE(4) DPC_CASE(5) DPC_CASE(6) DPC_CASE(7) DPC_CASE(8)
-
   }
   if constexpr (!kFromD) {
     switch (S) {
