@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 #include <rocblas/rocblas.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 
@@ -190,13 +191,16 @@ __device__ __forceinline__ void st4(double* p, D4 v) {
 // from memory itself.  Rows of the LDS copy are 4 doubles past a multiple of 8
 // apart: two K indices' rows fall into different halves of the banks.
 // Workgroups that share atoms run on one XCD (they read the same X).
+// Four channel tiles (the last group has three) fill the CUs where five leave a
+// quarter of them idle: 4,000 atoms, n_in 2,048, energy and gradient 245 / 228 us
+// with 5 / 4 (224 through rocBLAS), 8,000: 406 / 392 with 3 / 4 (421).
 template <int CT, int KC>
 __global__ __launch_bounds__(256, 2) void fit_layer1_kernel(int n, int nin, int nag,
                                                             const double* __restrict__ X,
                                                             const double* __restrict__ W,
                                                             const double* __restrict__ bias,
                                                             double* __restrict__ t1) {
-  constexpr int kGroups = kFt / CT, kLd = 16 * CT + 4, kSub = KC / 16;
+  constexpr int kGroups = (kFt + CT - 1) / CT, kLd = 16 * CT + 4, kSub = KC / 16;
   constexpr int kUnits = KC * CT * 8, kPer = (kUnits + 255) / 256;   // 16-byte pieces of a stage
   __shared__ __align__(16) double sW[2][KC * kLd];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -208,13 +212,19 @@ __global__ __launch_bounds__(256, 2) void fit_layer1_kernel(int n, int nin, int 
   const int atom = ag * 64 + wave * 16 + i;
   const double* Xa = X + (size_t)min(atom, n - 1) * nin;
   const double* Wc = W + cg * CT * 16;
+  // the last column a 16-byte piece may start at (CT = 4: the last group's
+  // fourth tile does not exist; existing columns are read in its place and its
+  // results not stored)
+  const int cmax = min(CT * 16, kFw - cg * CT * 16) - 2;
   D2 w[kPer];
   D4 x[kSub], xn[kSub];
   auto load = [&](int k0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
       const int e = (int)threadIdx.x + 256 * u, row = e / (CT * 8), c = e % (CT * 8);
-      w[u] = *reinterpret_cast<const D2*>(Wc + (size_t)min(k0 + row, nin - 1) * kFw + 2 * (e < kUnits ? c : 0));
+      const int col = 2 * (e < kUnits ? c : 0);
+      w[u] = *reinterpret_cast<const D2*>(Wc + (size_t)min(k0 + row, nin - 1) * kFw +
+                                          (kFt % CT == 0 ? col : min(col, cmax)));
     }
 #pragma unroll
     for (int s = 0; s < kSub; ++s) xn[s] = ld4(Xa + min(k0 + 16 * s + 4 * kk, nin - 4));
@@ -258,6 +268,7 @@ __global__ __launch_bounds__(256, 2) void fit_layer1_kernel(int n, int nin, int 
   const double* bc = bias + cg * CT * 16 + 4 * kk;
 #pragma unroll
   for (int c = 0; c < CT; ++c) {
+    if (kFt % CT != 0 && cg * CT + c >= kFt) continue;
     D4 v;
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] = tanh_e(acc[c][r] + bc[16 * c + r]);
@@ -696,13 +707,15 @@ int fit_240(hipStream_t s, int n, const dpc_fitting_net* net, const double* D, d
   if (n <= 2048) return fit_240_small(s, n, net, D, ws, np, E, dD);
   double *t1 = ws, *dz1 = ws + np;
   {
-    auto cost = [&](int ct) { return ceil_div(nag * (kFt / ct), kCus) * ct; };
+    auto cost = [&](int ct) { return ceil_div(nag * ceil_div(kFt, ct), kCus) * ct; };
     auto go = [&](auto kern, int ct) {
-      hipLaunchKernelGGL(kern, dim3(kXcd * ceil_div(nag, kXcd) * (kFt / ct)), dim3(256), 0, s, n, nin, nag, D,
+      hipLaunchKernelGGL(kern, dim3(kXcd * ceil_div(nag, kXcd) * ceil_div(kFt, ct)), dim3(256), 0, s, n, nin, nag, D,
                          net->W[0], net->b[0], t1);
     };
-    if (cost(15) <= cost(5) && cost(15) <= cost(3)) go(fit_layer1_kernel<15, 16>, 15);
-    else if (cost(5) <= cost(3)) go(fit_layer1_kernel<5, 32>, 5);
+    const int best = std::min(std::min(cost(15), cost(5)), std::min(cost(4), cost(3)));
+    if (cost(15) == best) go(fit_layer1_kernel<15, 16>, 15);
+    else if (cost(5) == best) go(fit_layer1_kernel<5, 32>, 5);
+    else if (cost(4) == best) go(fit_layer1_kernel<4, 32>, 4);
     else go(fit_layer1_kernel<3, 32>, 3);
   }
   auto middle = [&](auto kern, auto mt_, auto nw_) {

@@ -84,6 +84,18 @@ def test_input_widths(m1, m2):
         assert eE <= TOL and eG <= TOL and np.isfinite(E[ok]).all() and np.isfinite(G[ok]).all()
 
 
+@pytest.mark.parametrize("n", [3841, 4000, 4096, 7700, 8000])
+@pytest.mark.parametrize("m1,m2", [(5, 4), (100, 16)])
+def test_layer_of_four_tiles(n, m1, m2):
+    # atom counts whose first layer runs in four groups of channel tiles, of which the last has three
+    net = Net(m1 * m2, 240, n + m1)
+    D = np.random.default_rng(n).standard_normal((n, m1, m2))
+    E, G = net.run(D)
+    pick = np.r_[0:n:max(1, n // 400), n - 65:n]
+    eE, eG = _errors(net.net, D[pick], E[pick], G[pick])
+    assert eE <= TOL and eG <= TOL and np.isfinite(E).all() and np.isfinite(G).all()
+
+
 @pytest.mark.parametrize("m1,m2,width,shift", [(7, 3, 240, 0), (9, 6, 240, 0), (20, 4, 240, 1), (20, 4, 256, 0),
                                                (20, 4, 48, 0)])
 def test_general_path(m1, m2, width, shift):
