@@ -9,8 +9,9 @@
 //
 // Width 240 (the paper's) runs in three kernels on the float64 matrix cores:
 // layer 1 (n_in x 240, bias and tanh as it finishes), the middle of the net
-// (layers 2 and 3, the energy, and the backward of both, with everything but
-// the weights in registers and LDS) and dE/dx.  Other widths, an n_in that is
+// (layers 2 and 3, the energy, and the backward of both; the activations of a
+// workgroup's atoms stay in registers and LDS, but for 22 registers that the
+// shape for large systems spills) and dE/dx.  Other widths, an n_in that is
 // not a multiple of 4 and unaligned buffers go through plain GEMMs (rocBLAS,
 // on the caller's handle) with atoms as the long dimension and four streaming
 // kernels: bias + tanh (layer 1), bias + tanh + residual (layer 2), layer 3
@@ -165,8 +166,8 @@ __global__ __launch_bounds__(256) void tanh_grad_kernel(int64_t nw, int w, const
 // 240-wide side wastes a sixteenth of the 128-wide tiles, 96 tiles for 12,288
 // atoms leave most of the chip idle, and the products need ten passes over the
 // activations between them.  Energy and dE/dD, n_in 1,600, us through rocBLAS
-// and here: 256 atoms 149 / 52, 1,000: 121 / 111, 2,048: 157 / 158, 4,096:
-// 237 / 227, 12,288: 629 / 518, 131,072: 5,201 / 4,460, 1,048,576: 39,700 / 35,100.
+// and here: 256 atoms 147 / 49, 1,000: 114 / 104, 2,048: 146 / 146, 4,000:
+// 214 / 193, 12,288: 580 / 456, 131,072: 5,190 / 4,440, 1,048,576: 39,700 / 35,100.
 constexpr int kXcd = 8;                    // workgroups go to the XCDs in turn
 
 typedef double D2 __attribute__((ext_vector_type(2)));
