@@ -34,6 +34,7 @@ def log(*a):
 def kernel_source_hash(kernel="se_a"):
     src = ("dpc_descriptor.hip" if kernel.startswith("descriptor") else
            "dpc_env.hip" if kernel in ("env_mat_kernel", "force_kernel", "reverse_kernel") else
+           "dpc_nlist.hip" if kernel.startswith("nl_") else
            "dpc_se_a.hip")
     p = os.path.join(ROOT, "paper_2107_02103_amd", "csrc", src)
     return hashlib.sha256(open(p, "rb").read()).hexdigest()[:16]
