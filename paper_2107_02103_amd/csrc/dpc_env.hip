@@ -140,8 +140,8 @@ __global__ __launch_bounds__(256) void env_mat_kernel(const EnvGeo g, int chunks
 // which the lanes that missed read next.  What is still missing (lists in
 // another order) is looked for by the whole wavefront in all of the block.
 // Each lane reads a line of its own, about 34 GB of lines on 1,048,576 atoms
-// with 180 neighbours (512 slots): the kernel is bound by that traffic
-// (address unit 87% busy; 8 or 12 entries first and the misses packed again
+// with 180 neighbours (512 slots; 6.3 GB of them come from HBM): the kernel is
+// bound by that traffic (address unit 87% busy; 8 or 12 entries first and the misses packed again
 // gave 3.4 and 3.7 ms).  Both directions of a pair are searched, because a
 // coalesced row of results is cheaper than writing the partner's entry.
 // 13.6 ms with a search of one pair at a time by the whole wavefront, now 3.3.

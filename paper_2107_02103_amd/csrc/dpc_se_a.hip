@@ -1960,9 +1960,6 @@ int launch_fwd(hipStream_t s, const Geo& g, const void* coeff, const int* atype,
   }
 }
 
-// float64 or mixed: the matrix-core kernel, ceil(M1 / 16) K steps
-// per channel block, an interval copied by mfma_slot_kib(S, ld, esize) loads
-// (ld lies in [16 S - 12, 16 S], so that count takes one of two values per S)
 // What the rules below ever ask for: the mixed mode stops at 208 channels, and
 // shares only runs above 128.
 template <typename TI, int S, int NB, int kSplit>
@@ -1970,6 +1967,9 @@ constexpr bool mfma_wanted() {
   return sizeof(TI) == 8 || (S <= 13 && (S <= kMfmaWide || kSplit == 1 || NB == 1));
 }
 
+// float64 or mixed: the matrix-core kernel, ceil(M1 / 16) K steps
+// per channel block, an interval copied by mfma_slot_kib(S, ld, esize) loads
+// (ld lies in [16 S - 12, 16 S], so that count takes one of two values per S)
 template <typename TI, typename TO, int S, bool kFromD, int NB, int kSplit>
 void launch_mfma_s(hipStream_t s, const Geo& g, dim3 grid, const void* coeff,
                    const int* atype, const int* nlist, const void* em, const void* dT, void* dR,
